@@ -522,7 +522,8 @@ const char* rqc_version(void);
  * this plan launch their kernels directly on the caller's stream instead of
  * replaying a graph, and every probed launch is bracketed by a pair of HIP
  * events recorded on that stream; -1 turns the probe off and restores graph
- * launches. */
+ * launches.  Small steps that run inside a fused-subtree launch have no launch
+ * of their own and are not probed. */
 rqc_status rqc_plan_set_timing(rqc_plan* p, int32_t kernel);
 
 typedef struct rqc_timing {

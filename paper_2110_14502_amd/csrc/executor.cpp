@@ -329,6 +329,7 @@ void select_steps(rqc_plan* p) {
       p->sel_desc[m][i] = d;
       p->sel_kern[m][i] = k;
     }
+    p->chain[m] = plan_chains(p, m);
   }
   p->layouts.clear();
   clear_graphs(p);
@@ -431,6 +432,15 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
   const bool lp_mode = prec != RQC_F32;
   const int lp_store = prec == RQC_F16 ? ST_F16 : ST_BF16;
   std::vector<int64_t> bytes(nn, 0);
+  const ChainPlan& ch = p->chain[prec];
+  // Tensors inside a fused subtree have no place in memory: its own steps
+  // but the root, and the leaves that only such steps read.
+  std::vector<char> inside(nn, 0);
+  for (const ChainTree& t : ch.trees) {
+    for (size_t i = 0; i + 1 < t.steps.size(); ++i) inside[pd.steps[t.steps[i]].node] = 1;
+    for (int x : t.inputs)
+      if (x < nl) inside[x] = 1;
+  }
   for (int v = 0; v < nn; ++v) {
     Placement& P = L.place[v];
     P.dep_s = pd.dep_s[v];
@@ -446,6 +456,7 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
       P.e_off = p->inv_exp_off + 4 * v;
       continue;
     }
+    if (inside[v]) continue;
     const int cs = P.dep_s ? gs : 1, cb = P.dep_b ? gb : 1;
     const bool lp16 = v >= nl && step_lp_store(p, prec, (size_t)pd.step_of_node[v]);
     P.store = (lp_mode && lp16) ? lp_store : ST_C64;
@@ -483,12 +494,25 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
       }
   };
   for (int v = 0; v < nl; ++v)
-    if (!L.place[v].resident) L.place[v].off = alloc(bytes[v]);
+    if (!L.place[v].resident && !inside[v]) L.place[v].off = alloc(bytes[v]);
+  // Subtrees of leaves and resident tensors run first, in one launch.
+  for (const ChainTree& t : ch.trees) {
+    const int root = pd.steps[t.steps.back()].node;
+    if (t.first) L.place[root].off = alloc(bytes[root]);
+  }
   L.ksplit.assign(pd.steps.size(), 0);
   L.p_off.assign(pd.steps.size(), -1);
   for (size_t i = 0; i < pd.steps.size(); ++i) {
     const Step& st = pd.steps[i];
     if (st.invariant) continue;
+    if (ch.tree_of_step[i] >= 0) {
+      const ChainTree& t = ch.trees[ch.tree_of_step[i]];
+      if (t.first || t.steps.back() != (int)i) continue;
+      L.place[st.node].off = alloc(bytes[st.node]);
+      for (int x : t.inputs)
+        if (!L.place[x].resident && !inside[x]) release(L.place[x].off);
+      continue;
+    }
     L.place[st.node].off = alloc(bytes[st.node]);
     // Split-K for generic steps whose output tiles cannot fill the GPU.
     const StepDesc& t = p->sel_desc[prec][i];
@@ -520,33 +544,92 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
     sliced[pd.sliced[j]] = 1;
     slice_bit[pd.sliced[j]] = (int)j;
   }
+  // Selectors of a leaf: address bits fixed by the slice id or the bitstring.
+  auto selectors = [&](int v, int8_t* sel_pos, int16_t* sel_src) {
+    const Leaf& leaf = pd.net.leaves[v];
+    int n = 0;
+    for (int x : leaf.labels) {
+      const bool closed = pd.net.labels[x].kind == CLOSED;
+      if (!closed && !sliced[x]) continue;
+      sel_pos[n] = (int8_t)pos_in(leaf.labels, x);
+      sel_src[n] = closed ? (int16_t)(-pd.net.closed_col[x] - 1) : (int16_t)slice_bit[x];
+      ++n;
+    }
+    return n;
+  };
+  auto leaf_pos = [&](int v, int8_t* pos) {
+    const std::vector<int>& lay = pd.layout[v];
+    for (size_t i = 0; i < lay.size(); ++i)
+      pos[i] = (int8_t)pos_in(pd.net.leaves[v].labels, lay[lay.size() - 1 - i]);
+    return (int)lay.size();
+  };
+  std::vector<LeafJob> jobs;
   for (int v = 0; v < nl; ++v) {
     const Placement& P = L.place[v];
-    if (P.resident) continue;
-    const Leaf& leaf = pd.net.leaves[v];
+    if (P.resident || inside[v]) continue;
     LeafJob J;
     std::memset(&J, 0, sizeof J);
     J.src = p->leaf_store_off[v];
     J.dst = P.off / 8;
-    const std::vector<int>& lay = pd.layout[v];
-    J.rank = (int)lay.size();
-    for (int i = 0; i < J.rank; ++i) J.pos[i] = (int8_t)pos_in(leaf.labels, lay[J.rank - 1 - i]);
-    J.nsel = 0;
-    for (int x : leaf.labels) {
-      const bool closed = pd.net.labels[x].kind == CLOSED;
-      if (!closed && !sliced[x]) continue;
-      J.sel_pos[J.nsel] = (int8_t)pos_in(leaf.labels, x);
-      J.sel_src[J.nsel] = closed ? (int16_t)(-pd.net.closed_col[x] - 1) : (int16_t)slice_bit[x];
-      J.nsel++;
-    }
+    J.rank = leaf_pos(v, J.pos);
+    J.nsel = selectors(v, J.sel_pos, J.sel_src);
     J.dep_s = P.dep_s;
     J.dep_b = P.dep_b;
     J.dst_store = ST_C64;
     J.out_s = (int32_t)P.s_stride;
     J.out_b = (int32_t)P.b_stride;
-    L.max_leaf_rank = std::max(L.max_leaf_rank, J.rank);
-    L.jobs.push_back(J);
+    jobs.push_back(J);
   }
+  // Fused subtrees.
+  std::vector<ChainComp> comps;
+  std::vector<ChainInput> inputs;
+  std::vector<ChainStep> csteps;
+  for (const ChainTree& t : ch.trees) {
+    const Placement& R = L.place[pd.steps[t.steps.back()].node];
+    ChainComp c{};
+    c.dst = R.off;
+    c.s_stride = R.s_stride, c.b_stride = R.b_stride;
+    c.e_off = R.e_off, c.m_off = R.m_off;
+    c.es = R.es, c.eb = R.eb;
+    c.dep_s = R.dep_s, c.dep_b = R.dep_b;
+    c.input0 = (int32_t)inputs.size(), c.n_inputs = (int32_t)t.inputs.size();
+    c.step0 = (int32_t)csteps.size(), c.n_steps = (int32_t)t.prog.size();
+    comps.push_back(c);
+    csteps.insert(csteps.end(), t.prog.begin(), t.prog.end());
+    for (size_t i = 0; i < t.inputs.size(); ++i) {
+      const int x = t.inputs[i];
+      const Placement& P = L.place[x];
+      ChainInput in;
+      std::memset(&in, 0, sizeof in);
+      in.rank = (int32_t)pd.layout[x].size();
+      in.lds = t.input_lds[i];
+      in.max_const = P.max_const;
+      in.e_off = P.e_off, in.m_off = P.m_off;
+      in.es = P.es, in.eb = P.eb;
+      in.leaf = x < nl && !P.resident;
+      in.resident = P.resident;
+      if (in.leaf) {
+        in.src = p->leaf_store_off[x];
+        leaf_pos(x, in.pos);
+        in.nsel = selectors(x, in.sel_pos, in.sel_src);
+      } else {
+        in.src = P.off;
+        in.s_stride = P.s_stride, in.b_stride = P.b_stride;
+      }
+      inputs.push_back(in);
+    }
+  }
+  L.n_jobs = (int)jobs.size();
+  auto put = [&](const void* src, size_t n) {
+    const int64_t at = (int64_t)L.blob.size();
+    L.blob.resize((size_t)align256(at + (int64_t)n));
+    if (n) std::memcpy(L.blob.data() + at, src, n);
+    return at;
+  };
+  put(jobs.data(), sizeof(LeafJob) * jobs.size());
+  L.comps_off = put(comps.data(), sizeof(ChainComp) * comps.size());
+  L.inputs_off = put(inputs.data(), sizeof(ChainInput) * inputs.size());
+  L.csteps_off = put(csteps.data(), sizeof(ChainStep) * csteps.size());
   return L;
 }
 
@@ -570,7 +653,7 @@ WsLayout ws_layout(rqc_plan* p, const GroupLayout& L, uint64_t n_ids, uint64_t n
   w.flags_off = o;
   o = align256(o + 4 * (int64_t)n_ids * w.n_bgroups);
   w.jobs_off = o;
-  o = align256(o + (int64_t)sizeof(LeafJob) * (int64_t)std::max<size_t>(1, L.jobs.size()));
+  o = align256(o + (int64_t)L.blob.size());
   w.tmp_off = o;
   o = align256(o + 16 * (int64_t)n_batch * (int64_t(1) << pd.net.open.size()));
   w.scale_off = o;
@@ -645,7 +728,6 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
                  uint64_t n_batch, char* ws, double* out, double* per_slice, int64_t ps_row0,
                  hipStream_t s) {
   PlanData& pd = p->pd;
-  const bool track = true;                  // exponents in every precision
   const bool lp_mode = L.prec != RQC_F32;   // slice flags drive FP32 re-runs
   char* arena = ws + W.arena_off;
   char* scale = ws + W.scale_off;
@@ -660,7 +742,29 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
     if (P.e_off < 0) return nullptr;
     return reinterpret_cast<int32_t*>(P.resident ? p->res + P.e_off : scale + P.e_off);
   };
-  hip_check(launch_fill_i32(flags, 0, (int64_t)n_ids * W.n_bgroups, s), "clear flags");
+  const ChainPlan& ch = p->chain[L.prec];
+  const char* blob = ws + W.jobs_off;
+  ChainArgs ca{};
+  ca.comps = reinterpret_cast<const ChainComp*>(blob + L.comps_off);
+  ca.inputs = reinterpret_cast<const ChainInput*>(blob + L.inputs_off);
+  ca.steps = reinterpret_cast<const ChainStep*>(blob + L.csteps_off);
+  ca.res = p->res;
+  ca.arena = arena;
+  ca.scale = scale;
+  ca.n_closed = n_closed;
+  // Subtrees [first, first + n) of the chain plan for one group.
+  auto run_chains = [&](int first, int n) {
+    int copies = 1;
+    for (int c = first; c < first + n; ++c) {
+      const Step& r = pd.steps[ch.trees[c].steps.back()];
+      copies = std::max(copies, (r.dep_s ? ca.gs : 1) * (r.dep_b ? ca.gb : 1));
+    }
+    ChainArgs a = ca;
+    a.comps += first;
+    hip_check(launch_chain(a, n, copies, ch.lds_elems, s), "fused subtrees");
+  };
+  int n_first = 0;
+  while (n_first < (int)ch.trees.size() && ch.trees[n_first].first) ++n_first;
   size_t probe = 0;
   p->trec.clear();
   for (uint64_t b0 = 0; b0 < n_batch; b0 += L.gb) {
@@ -670,16 +774,26 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
     const int bias = b0 >= p->scale_bias_from ? p->scale_bias : 0;
     for (uint64_t g0 = 0; g0 < n_ids; g0 += L.gs) {
       const int gsc = (int)std::min<uint64_t>(L.gs, n_ids - g0);
-      if (track && L.scale_bytes > 0)
-        hip_check(launch_fill_i32(reinterpret_cast<int32_t*>(scale), 0, L.scale_bytes / 4, s),
-                  "clear scales");
-      hip_check(launch_leaves(jobs, (int)L.jobs.size(), p->res, arena, ids + g0,
-                              bits + b0 * (uint64_t)std::max(1, n_closed), n_closed, gsc, gbc,
-                              L.max_leaf_rank, s),
-                "leaves");
+      const bool first_group = b0 == 0 && g0 == 0;
+      const uint8_t* gbits = bits + b0 * (uint64_t)std::max(1, n_closed);
+      hip_check(launch_prologue(jobs, L.n_jobs, p->res, arena, ids + g0, gbits, n_closed, gsc, gbc,
+                                flags, first_group ? (int64_t)n_ids * W.n_bgroups : 0,
+                                reinterpret_cast<int32_t*>(scale), L.scale_bytes / 4, s),
+                "leaves and clears");
+      ca.slice_ids = ids + g0;
+      ca.closed = gbits;
+      ca.flag = gflags + g0;
+      ca.gs = gsc;
+      ca.gb = gbc;
+      run_chains(0, n_first);
       for (size_t i = 0; i < pd.steps.size(); ++i) {
         const Step& st = pd.steps[i];
         if (st.invariant) continue;
+        if (ch.tree_of_step[i] >= 0) {
+          const ChainTree& t = ch.trees[ch.tree_of_step[i]];
+          if (!t.first && t.steps.back() == (int)i) run_chains(ch.tree_of_step[i], 1);
+          continue;
+        }
         StepDesc d = bind_step(p, L, W, ws, i, gsc, gbc, gflags + g0, bias);
         const Placement &A = L.place[st.a], &B = L.place[st.b], &C = L.place[st.node];
         const int kern = p->sel_kern[L.prec][i];
@@ -796,10 +910,9 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
   char* ws = static_cast<char*>(ws_v);
   hip_check(hipMemcpyAsync(ws + W.ids_off, ids.data(), 8 * n_ids, hipMemcpyHostToDevice, s), "ids");
   hip_check(hipMemcpyAsync(ws + W.bits_off, b.data(), b.size(), hipMemcpyHostToDevice, s), "bits");
-  if (!L.jobs.empty())
-    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.jobs.data(), sizeof(LeafJob) * L.jobs.size(),
-                             hipMemcpyHostToDevice, s),
-              "jobs");
+  if (!L.blob.empty())
+    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s),
+              "program");
   GraphKey key{prec, gs, gb, n_ids, n_batch, ws_v, out, per_slice};
   auto it = p->graphs.find(key);
   int reused = 0;
@@ -923,10 +1036,10 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
     const uint64_t id = r.ids[idx];
     hip_check(hipMemcpyAsync(r.ws + W.ids_off, &id, 8, hipMemcpyHostToDevice, s), "ids");
     hip_check(hipMemcpyAsync(r.ws + W.bits_off, r.bits.data(), r.bits.size(), hipMemcpyHostToDevice, s), "bits");
-    if (!L.jobs.empty())
-      hip_check(hipMemcpyAsync(r.ws + W.jobs_off, L.jobs.data(), sizeof(LeafJob) * L.jobs.size(),
+    if (!L.blob.empty())
+      hip_check(hipMemcpyAsync(r.ws + W.jobs_off, L.blob.data(), L.blob.size(),
                                hipMemcpyHostToDevice, s),
-                "jobs");
+                "program");
     record_call(p, L, W, 1, r.n_batch, r.ws, tmp, nullptr, 0, s);
     for (int64_t g = 0; g < nbg; ++g) {
       if (!flags[(size_t)(g * (int64_t)r.n_ids + (int64_t)idx)]) continue;

@@ -25,14 +25,33 @@ struct Placement {
   bool dep_s = false, dep_b = false;
 };
 
+// Steps evaluated inside fused small subtrees (k_chain.hip) in one precision
+// mode: the subtrees' steps in execution order, their inputs, and where every
+// tensor sits in LDS.  Independent of the group size.
+struct ChainTree {
+  std::vector<int> steps;              // plan steps, the last one makes the root
+  std::vector<int> inputs;             // tree nodes read from memory
+  std::vector<ChainStep> prog;         // per step
+  std::vector<int> input_lds;          // per input
+  bool first = false;                  // inputs are leaves and resident tensors only
+};
+struct ChainPlan {
+  std::vector<ChainTree> trees;        // `first` ones first, then by root step
+  std::vector<int> tree_of_step;       // -1: the step is launched by itself
+  int lds_elems = 0;                   // largest subtree
+};
+
 // Memory layout of one (precision, slices per group, bits per group).
 struct GroupLayout {
   int prec = RQC_F32, gs = 1, gb = 1;
   std::vector<Placement> place;  // per tree node
   int64_t arena_bytes = 0;       // variable tensors
   int64_t scale_bytes = 0;       // exponent / max arrays
-  std::vector<LeafJob> jobs;     // variable leaves
-  int max_leaf_rank = 0;
+  int n_jobs = 0;                // variable leaves read by steps of their own
+  // Device program of the call, uploaded as one block: leaf jobs, then the
+  // fused subtrees' components, inputs and steps at the given byte offsets.
+  std::vector<char> blob;
+  int64_t comps_off = 0, inputs_off = 0, csteps_off = 0;
   std::vector<int> ksplit;       // per step: split-K bits (generic kernel)
   std::vector<int64_t> p_off;    // per step: partial buffer in the arena
 };
@@ -114,6 +133,7 @@ struct rqc_plan {
   std::vector<int> tuned_kern[3], tuned_var[3];
   std::vector<rqc::StepDesc> sel_desc[3];
   std::vector<int> sel_kern[3];
+  rqc::ChainPlan chain[3];              // fused small subtrees per precision mode
   // Timing probe: events around launches of one kernel kind (or of all).
   int timing_kernel = -1;
   int group_limit_s = 0, group_limit_b = 0;  // 0: bounded by the workspace only
@@ -149,7 +169,7 @@ void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_
 bool fits(rqc_plan* p, int prec, int gs, int gb, uint64_t n_ids, uint64_t n_batch,
           size_t ws_bytes);
 
-// Every launch of one call (ids, bits and leaf jobs already in the
+// Every launch of one call (ids, bits and the device program already in the
 // workspace), in order on `s`.
 void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t n_ids,
                  uint64_t n_batch, char* ws, double* out, double* per_slice, int64_t ps_row0,
@@ -199,6 +219,10 @@ void clear_graphs(rqc_plan* p);
 // defaults, the precision policy, the per-step reduced-precision switches and
 // the tuner's choices; drops cached layouts and graphs.
 void select_steps(rqc_plan* p);
+
+// The fused small subtrees of mode `prec` under the current storage choices
+// (chain.cpp).
+ChainPlan plan_chains(const rqc_plan* p, int prec);
 
 // Whether step i stores its output in 16 bits in mode `prec`.
 bool step_lp_store(const rqc_plan* p, int prec, size_t i);

@@ -86,6 +86,61 @@ struct LeafJob {
   int32_t out_s, out_b;  // copy strides of the destination (elements)
 };
 
+// Fused small subtrees (k_chain.hip): one workgroup evaluates one subtree for
+// one copy with every tensor in LDS.  Limits of one subtree; the tensors
+// share kChainMaxElems complex values of LDS (54 KB, which with the program
+// and the scale slots stays below 64 KB).
+constexpr int kChainMaxSteps = 128, kChainMaxSlots = 288, kChainMaxElems = 6912;
+
+// One input tensor of a subtree: a leaf (bound from the leaf store by the
+// slice's and the bitstring's selector bits) or a computed tensor.
+struct ChainInput {
+  int64_t src;                  // leaf: element offset in the leaf store; else bytes from its region
+  int64_t s_stride, b_stride;   // copy strides, elements
+  int64_t e_off, m_off;         // bytes of the scale arrays in its region (-1: none)
+  int32_t es, eb;               // copy strides of the scale arrays
+  int32_t leaf, resident;       // region: the plan's resident memory or the call's arena
+  int32_t rank, lds;            // 2^rank elements at LDS element lds
+  int32_t nsel;                 // leaf: as in LeafJob
+  float max_const;
+  int8_t pos[8], sel_pos[8];
+  int16_t sel_src[8];
+};
+
+// One step of a subtree: tensors at LDS elements lds_*, scale slots (inputs
+// first, then the steps in order); rpos / cpos: address bit in C of row /
+// column bit i (0 past the step's own).
+struct ChainStep {
+  uint16_t lds_a, lds_b, lds_c, slot_a, slot_b;
+  uint8_t m, n, k, pad;
+  int8_t rpos[12], cpos[12];
+  uint16_t pad2;
+};
+static_assert(sizeof(ChainStep) == 40, "copied as words");
+
+// One subtree: its program and where its root goes (arena bytes, copy
+// strides in elements, scale arrays).
+struct ChainComp {
+  int64_t dst, s_stride, b_stride, e_off, m_off;
+  int32_t es, eb, dep_s, dep_b;
+  int32_t input0, n_inputs, step0, n_steps;
+};
+
+struct ChainArgs {
+  const ChainComp* comps;
+  const ChainInput* inputs;
+  const ChainStep* steps;
+  const char* res;
+  char* arena;
+  char* scale;
+  const uint64_t* slice_ids;
+  const uint8_t* closed;
+  int32_t* flag;
+  int32_t n_closed, gs, gb;
+};
+
+hipError_t launch_chain(const ChainArgs& a, int n_comps, int max_copies, int lds_elems, hipStream_t s);
+
 // Kernel variant bits of a step (StepDesc::variant).  FP32 matrix-core
 // kernel: the complex products as four real products on the real expansion
 // of B (kVar4M) or as three (the default); one tile per workgroup
@@ -119,9 +174,13 @@ inline bool lp_vec_layout(const StepDesc& d) {
 
 hipError_t launch_step(const StepDesc& d, int kernel, int sa, int sb, int sc, int lp_kind,
                        hipStream_t s);
-hipError_t launch_leaves(const LeafJob* jobs_dev, int n_jobs, const void* leaf_store,
-                         void* dst_base, const uint64_t* slice_ids, const uint8_t* closed_bits,
-                         int n_closed, int gs, int gb, int max_rank, hipStream_t s);
+// Start of a group: the leaves that steps read from memory are instantiated,
+// and the scale arrays and (n_flags > 0: the call's first group) the flags
+// are cleared, all in one launch.
+hipError_t launch_prologue(const LeafJob* jobs_dev, int n_jobs, const void* leaf_store,
+                           void* dst_base, const uint64_t* slice_ids, const uint8_t* closed_bits,
+                           int n_closed, int gs, int gb, int32_t* flags, int64_t n_flags,
+                           int32_t* scale, int64_t n_scale, hipStream_t s);
 hipError_t launch_slice_sum(const void* root, int root_store, const int32_t* root_exp,
                             int64_t root_s, int64_t root_b, int32_t re_s, int32_t re_b,
                             int dep_s, int dep_b, int n_elems, int gs, int gb,
@@ -132,8 +191,6 @@ hipError_t launch_slice_sum(const void* root, int root_store, const int32_t* roo
 // |a|^4, out[2..4] the linear cross-entropy values (see rqc_batch_xeb).
 hipError_t launch_batch_stats(const double* amps, uint64_t n, int n_qubits, const uint64_t* samples,
                               uint64_t n_samples, double* out, hipStream_t s);
-hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
-hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t launch_add_f64(double* dst, const double* src, int64_t n, hipStream_t s);
 // Bit permutation out (bit i fed by input bit src_pos_of_out_bit[i]) of a
 // complex64 tensor; out_store ST_F16 / ST_BF16 writes packed 16-bit (re, im)

@@ -27,9 +27,19 @@ hipError_t launch_step(const StepDesc& d0, int kernel, int sa, int sb, int sc, i
 // selectors to the requested bits (Section 5.1), producing one copy per
 // (slice, bitstring) of the group that the leaf depends on.
 // ---------------------------------------------------------------------------
-__global__ void k_leaves(const LeafJob* jobs, const float2* store, float2* dst,
-                         const uint64_t* slice_ids, const uint8_t* closed, int n_closed, int gs,
-                         int gb) {
+// Blocks past the jobs clear the call's flags and the group's scale arrays
+// (three launches of 1-4 us with 4-5 us gaps between them before).
+__global__ void k_prologue(const LeafJob* jobs, int n_jobs, const float2* store, float2* dst,
+                           const uint64_t* slice_ids, const uint8_t* closed, int n_closed, int gs,
+                           int gb, int32_t* flags, int64_t n_flags, int32_t* scale,
+                           int64_t n_scale) {
+  if ((int)blockIdx.x >= n_jobs) {
+    const int64_t i0 = (blockIdx.x - n_jobs) * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)(gridDim.x - n_jobs) * blockDim.x;
+    for (int64_t i = i0; i < n_flags; i += step) flags[i] = 0;
+    for (int64_t i = i0; i < n_scale; i += step) scale[i] = 0;
+    return;
+  }
   const LeafJob& J = jobs[blockIdx.x];
   const int ne = 1 << J.rank;
   const int cs = J.dep_s ? gs : 1;
@@ -52,14 +62,17 @@ __global__ void k_leaves(const LeafJob* jobs, const float2* store, float2* dst,
   }
 }
 
-hipError_t launch_leaves(const LeafJob* jobs_dev, int n_jobs, const void* leaf_store,
-                         void* dst_base, const uint64_t* slice_ids, const uint8_t* closed_bits,
-                         int n_closed, int gs, int gb, int max_rank, hipStream_t s) {
-  if (n_jobs <= 0) return hipSuccess;
-  (void)max_rank;
-  hipLaunchKernelGGL(k_leaves, dim3(n_jobs), dim3(256), 0, s, jobs_dev,
+hipError_t launch_prologue(const LeafJob* jobs_dev, int n_jobs, const void* leaf_store,
+                           void* dst_base, const uint64_t* slice_ids, const uint8_t* closed_bits,
+                           int n_closed, int gs, int gb, int32_t* flags, int64_t n_flags,
+                           int32_t* scale, int64_t n_scale, hipStream_t s) {
+  const int64_t n = n_flags > n_scale ? n_flags : n_scale;
+  int64_t fill = (n + 255) / 256;
+  if (fill > 4096) fill = 4096;
+  if (n_jobs + fill <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_prologue, dim3((unsigned)(n_jobs + fill)), dim3(256), 0, s, jobs_dev, n_jobs,
                      reinterpret_cast<const float2*>(leaf_store), reinterpret_cast<float2*>(dst_base),
-                     slice_ids, closed_bits, n_closed, gs, gb);
+                     slice_ids, closed_bits, n_closed, gs, gb, flags, n_flags, scale, n_scale);
   return hipGetLastError();
 }
 
@@ -128,18 +141,8 @@ hipError_t launch_slice_sum(const void* root, int root_store, const int32_t* roo
 }
 
 // ---------------------------------------------------------------------------
-// Small utility kernels (fills instead of memsets so that graphs replay them)
+// Small utility kernel: adds an FP32 re-run to the sums that skipped it
 // ---------------------------------------------------------------------------
-__global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-__global__ void k_fill_f64(double* p, double v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
 __global__ void k_add_f64(double* d, const double* s, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -153,16 +156,6 @@ static dim3 fill_grid(int64_t n) {
   return dim3((unsigned)b);
 }
 
-hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_i32, fill_grid(n), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
-hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_f64, fill_grid(n), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
 hipError_t launch_add_f64(double* dst, const double* src, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_add_f64, fill_grid(n), dim3(256), 0, s, dst, src, n);

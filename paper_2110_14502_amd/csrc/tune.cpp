@@ -102,10 +102,9 @@ void copy_call_inputs(rqc_plan* p, const GroupLayout& L, const WsLayout& W, char
                       hipStream_t s) {
   hip_check(hipMemcpyAsync(ws + W.ids_off, ids.data(), 8 * ids.size(), hipMemcpyHostToDevice, s), "ids");
   hip_check(hipMemcpyAsync(ws + W.bits_off, bits.data(), bits.size(), hipMemcpyHostToDevice, s), "bits");
-  if (!L.jobs.empty())
-    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.jobs.data(), sizeof(LeafJob) * L.jobs.size(),
-                             hipMemcpyHostToDevice, s),
-              "jobs");
+  if (!L.blob.empty())
+    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s),
+              "program");
 }
 
 struct Events {
@@ -164,7 +163,7 @@ void autotune(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, void* ws_
   Events ev;
   std::vector<std::pair<std::string, std::pair<int, int>>> learned;
   for (size_t i = 0; i < pd.steps.size(); ++i) {
-    if (pd.steps[i].invariant) continue;
+    if (pd.steps[i].invariant || p->chain[prec].tree_of_step[i] >= 0) continue;
     const auto cand = candidates(p, prec, i);
     if (cand.empty()) continue;
     rep->steps++;
