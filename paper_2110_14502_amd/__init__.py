@@ -168,6 +168,8 @@ _PROTOS = {
                                   C.c_uint64, _P]),
     "rqc_permute": (_S, [C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_int32, _P, _P, _P]),
     "rqc_batch_xeb": (_S, [_P, C.c_uint64, C.c_int32, _P, C.c_uint64, _P, _P]),
+    "rqc_batch_xeb_workspace_bytes": (_S, [C.c_uint64, C.c_uint64, C.POINTER(C.c_uint64)]),
+    "rqc_batch_xeb_ws": (_S, [_P, C.c_uint64, C.c_int32, _P, C.c_uint64, _P, _P, C.c_uint64, _P]),
     "rqc_contract_noalloc": (_S, [_P, C.POINTER(C.c_uint64), C.c_uint64, C.POINTER(C.c_uint8),
                                   C.c_uint64, C.c_int32, _P, _P, _P]),
     "rqc_contract_noalloc_scratch_bytes": (C.c_uint64, []),
@@ -608,12 +610,16 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     returns; samples an int64 device tensor of entry indices or None."""
     import torch
     n = amps.numel() // 2
-    out = torch.empty(5, dtype=torch.float64, device=amps.device)
     ns = 0 if samples is None else samples.numel()
-    _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits),
-                              _ptr(samples) if samples is not None else None, ns, _ptr(out),
-                              _stream_handle(stream)))
-    v = out.cpu().numpy()
+    need = C.c_uint64()
+    _check(_lib.rqc_batch_xeb_workspace_bytes(n, ns, C.byref(need)))
+    # The five results, then the workspace (one buffer, so one lifetime).
+    out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
+    _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits),
+                                 _ptr(samples) if samples is not None else None, ns, _ptr(out),
+                                 C.c_void_p(out.data_ptr() + 64), need.value,
+                                 _stream_handle(stream)))
+    v = out[:5].cpu().numpy()
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 

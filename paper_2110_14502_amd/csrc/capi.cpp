@@ -689,16 +689,42 @@ rqc_status rqc_pair_contract_stored(const int32_t* labels_a, int32_t rank_a,
   RQC_CATCH
 }
 
+static void batch_xeb(const double* amps, uint64_t n_amps, int32_t n_qubits, const uint64_t* samples,
+                      uint64_t n_samples, double* out, void* ws, rqc_stream stream) {
+  if (!amps || !out) throw rqc::Error{RQC_EINVAL, "NULL device pointer"};
+  if (n_samples && !samples) throw rqc::Error{RQC_EINVAL, "samples is NULL"};
+  if (n_qubits < 1 || n_qubits > 1000) throw rqc::Error{RQC_EINVAL, "n_qubits out of range"};
+  rqc::hip_check(rqc::launch_batch_stats(amps, n_amps, n_qubits, samples, n_samples, out, ws,
+                                         static_cast<hipStream_t>(stream)),
+                 "batch statistics");
+}
+
 rqc_status rqc_batch_xeb(const double* amps, uint64_t n_amps, int32_t n_qubits,
                          const uint64_t* samples, uint64_t n_samples, double* out,
                          rqc_stream stream) {
   RQC_TRY
-  if (!amps || !out) throw rqc::Error{RQC_EINVAL, "NULL device pointer"};
-  if (n_samples && !samples) throw rqc::Error{RQC_EINVAL, "samples is NULL"};
-  if (n_qubits < 1 || n_qubits > 1000) throw rqc::Error{RQC_EINVAL, "n_qubits out of range"};
-  rqc::hip_check(rqc::launch_batch_stats(amps, n_amps, n_qubits, samples, n_samples, out,
-                                         static_cast<hipStream_t>(stream)),
-                 "batch statistics");
+  batch_xeb(amps, n_amps, n_qubits, samples, n_samples, out, nullptr, stream);
+  return RQC_OK;
+  RQC_CATCH
+}
+
+rqc_status rqc_batch_xeb_workspace_bytes(uint64_t n_amps, uint64_t n_samples, uint64_t* bytes) {
+  RQC_TRY
+  if (!bytes) throw rqc::Error{RQC_EINVAL, "NULL argument"};
+  *bytes = rqc::batch_stats_workspace(n_amps, n_samples);
+  return RQC_OK;
+  RQC_CATCH
+}
+
+rqc_status rqc_batch_xeb_ws(const double* amps, uint64_t n_amps, int32_t n_qubits,
+                            const uint64_t* samples, uint64_t n_samples, double* out,
+                            void* workspace, uint64_t ws_bytes, rqc_stream stream) {
+  RQC_TRY
+  const uint64_t need = rqc::batch_stats_workspace(n_amps, n_samples);
+  if (need && (!workspace || ws_bytes < need))
+    throw rqc::Error{RQC_EINVAL, "workspace smaller than rqc_batch_xeb_workspace_bytes"};
+  if ((uintptr_t)workspace % 8) throw rqc::Error{RQC_EINVAL, "workspace not 8-byte aligned"};
+  batch_xeb(amps, n_amps, n_qubits, samples, n_samples, out, workspace, stream);
   return RQC_OK;
   RQC_CATCH
 }

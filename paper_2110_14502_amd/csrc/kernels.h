@@ -188,9 +188,12 @@ hipError_t launch_slice_sum(const void* root, int root_store, const int32_t* roo
                             int64_t ps_row0, int64_t n_batch_total, int64_t b0, int first,
                             hipStream_t s);
 // FP64 statistics of an amplitude batch: out[0] = sum |a|^2, out[1] = sum
-// |a|^4, out[2..4] the linear cross-entropy values (see rqc_batch_xeb).
+// |a|^4, out[2..4] the linear cross-entropy values (see rqc_batch_xeb).  ws:
+// batch_stats_workspace bytes, or NULL for the one-workgroup form.
 hipError_t launch_batch_stats(const double* amps, uint64_t n, int n_qubits, const uint64_t* samples,
-                              uint64_t n_samples, double* out, hipStream_t s);
+                              uint64_t n_samples, double* out, void* ws, hipStream_t s);
+// Workspace (bytes) of its many-workgroup form; 0: one workgroup is faster.
+uint64_t batch_stats_workspace(uint64_t n, uint64_t n_samples);
 hipError_t launch_add_f64(double* dst, const double* src, int64_t n, hipStream_t s);
 // Bit permutation out (bit i fed by input bit src_pos_of_out_bit[i]) of a
 // complex64 tensor; out_store ST_F16 / ST_BF16 writes packed 16-bit (re, im)

@@ -383,43 +383,68 @@ hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src
 namespace rqc {
 
 // ---------------------------------------------------------------------------
-// Statistics of an amplitude batch in FP64 (one workgroup, fixed summation
-// order, so the result does not depend on timing): sum |a|^2, sum |a|^4, and
+// Statistics of an amplitude batch in FP64 (fixed summation order, so the result does not depend on timing): sum |a|^2, sum |a|^4, and
 // the linear cross-entropy values derived from them; optionally the mean
 // |a|^2 over sampled entries of the batch (bounds-checked: an index outside
 // the batch makes that result NaN).
+//
+// Batches above 2^13 amplitudes are read by many workgroups (rqc_batch_xeb_ws):
+// each writes four partial sums, and one workgroup adds them in workgroup
+// order; the split depends on the batch size alone.  One workgroup reads
+// 56 GB/s (601 us for 2^21 amplitudes, 33 MB); below 2^13 the second launch
+// costs more than the reading.
 // ---------------------------------------------------------------------------
 constexpr int kStatThreads = 1024;
 
-__global__ __launch_bounds__(kStatThreads) void k_batch_stats(const double* amps, uint64_t n,
-                                                               double dim, const uint64_t* samples,
-                                                               uint64_t n_samples, double* out) {
-  __shared__ double r1[kStatThreads], r2[kStatThreads], r3[kStatThreads];
-  __shared__ int bad_any[kStatThreads];
-  const int t = threadIdx.x;
-  double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  int bad = 0;
-  for (uint64_t i = t; i < n; i += kStatThreads) {
-    const double re = amps[2 * i], im = amps[2 * i + 1];
-    const double p = re * re + im * im;
-    s1 += p;
-    s2 += p * p;
+struct Stats {
+  double s1, s2, s3;  // sum p, sum p^2, sum p over samples
+  int bad;            // a sample index outside the batch
+};
+
+// Sums over entries first, first + stride, ... and the samples likewise.
+__device__ __forceinline__ Stats stat_range(const double* amps, uint64_t n, const uint64_t* samples,
+                                            uint64_t n_samples, uint64_t first, uint64_t stride) {
+  typedef double d2v __attribute__((ext_vector_type(2)));
+  Stats v{0.0, 0.0, 0.0, 0};
+  // Amplitudes are read as aligned 16-byte pairs where the buffer allows it.
+  const bool pairs = (reinterpret_cast<uintptr_t>(amps) & 15) == 0;
+#pragma unroll 4
+  for (uint64_t i = first; i < n; i += stride) {
+    d2v a;
+    if (pairs) {
+      a = reinterpret_cast<const d2v*>(amps)[i];
+    } else {
+      a[0] = amps[2 * i];
+      a[1] = amps[2 * i + 1];
+    }
+    const double p = a[0] * a[0] + a[1] * a[1];
+    v.s1 += p;
+    v.s2 += p * p;
   }
-  for (uint64_t j = t; j < n_samples; j += kStatThreads) {
+  for (uint64_t j = first; j < n_samples; j += stride) {
     const uint64_t i = samples[j];
     if (i >= n) {
-      bad = 1;
+      v.bad = 1;
       continue;
     }
     const double re = amps[2 * i], im = amps[2 * i + 1];
-    s3 += re * re + im * im;
+    v.s3 += re * re + im * im;
   }
-  r1[t] = s1;
-  r2[t] = s2;
-  r3[t] = s3;
-  bad_any[t] = bad;
+  return v;
+}
+
+// Sum over the workgroup in a fixed tree order; valid in thread 0.
+template <int T>
+__device__ __forceinline__ Stats stat_reduce(Stats v) {
+  __shared__ double r1[T], r2[T], r3[T];
+  __shared__ int bad_any[T];
+  const int t = threadIdx.x;
+  r1[t] = v.s1;
+  r2[t] = v.s2;
+  r3[t] = v.s3;
+  bad_any[t] = v.bad;
   __syncthreads();
-  for (int w = kStatThreads / 2; w > 0; w >>= 1) {
+  for (int w = T / 2; w > 0; w >>= 1) {
     if (t < w) {
       r1[t] += r1[t + w];
       r2[t] += r2[t + w];
@@ -428,21 +453,83 @@ __global__ __launch_bounds__(kStatThreads) void k_batch_stats(const double* amps
     }
     __syncthreads();
   }
-  if (t == 0) {
-    const double sum_p = r1[0], sum_p2 = r2[0];
-    out[0] = sum_p;
-    out[1] = sum_p2;
-    out[2] = n ? dim * sum_p / (double)n - 1.0 : 0.0;  // all entries taken as samples
-    out[3] = sum_p > 0.0 ? dim * sum_p2 / sum_p - 1.0 : 0.0;  // entries drawn with p = |a|^2
-    out[4] = n_samples == 0 ? 0.0
-             : (bad_any[0] ? __builtin_nan("") : dim * r3[0] / (double)n_samples - 1.0);
+  return Stats{r1[0], r2[0], r3[0], bad_any[0]};
+}
+
+__device__ __forceinline__ void stat_write(const Stats& v, uint64_t n, double dim, uint64_t n_samples,
+                                           double* out) {
+  out[0] = v.s1;
+  out[1] = v.s2;
+  out[2] = n ? dim * v.s1 / (double)n - 1.0 : 0.0;  // all entries taken as samples
+  out[3] = v.s1 > 0.0 ? dim * v.s2 / v.s1 - 1.0 : 0.0;  // entries drawn with p = |a|^2
+  out[4] = n_samples == 0 ? 0.0
+           : (v.bad ? __builtin_nan("") : dim * v.s3 / (double)n_samples - 1.0);
+}
+
+__global__ __launch_bounds__(kStatThreads) void k_batch_stats(const double* amps, uint64_t n,
+                                                               double dim, const uint64_t* samples,
+                                                               uint64_t n_samples, double* out) {
+  const Stats v =
+      stat_reduce<kStatThreads>(stat_range(amps, n, samples, n_samples, threadIdx.x, kStatThreads));
+  if (threadIdx.x == 0) stat_write(v, n, dim, n_samples, out);
+}
+
+__global__ __launch_bounds__(256) void k_batch_stats_part(const double* amps, uint64_t n,
+                                                          const uint64_t* samples,
+                                                          uint64_t n_samples, double* part) {
+  const Stats v = stat_reduce<256>(stat_range(amps, n, samples, n_samples,
+                                              (uint64_t)blockIdx.x * 256 + threadIdx.x,
+                                              (uint64_t)gridDim.x * 256));
+  if (threadIdx.x == 0) {
+    double* p = part + 4 * (uint64_t)blockIdx.x;
+    p[0] = v.s1;
+    p[1] = v.s2;
+    p[2] = v.s3;
+    p[3] = v.bad ? 1.0 : 0.0;
   }
 }
 
+__global__ __launch_bounds__(256) void k_batch_stats_sum(const double* part, int n_part, uint64_t n,
+                                                         double dim, uint64_t n_samples, double* out) {
+  Stats v{0.0, 0.0, 0.0, 0};
+  for (int i = threadIdx.x; i < n_part; i += 256) {
+    v.s1 += part[4 * i];
+    v.s2 += part[4 * i + 1];
+    v.s3 += part[4 * i + 2];
+    v.bad |= part[4 * i + 3] != 0.0;
+  }
+  v = stat_reduce<256>(v);
+  if (threadIdx.x == 0) stat_write(v, n, dim, n_samples, out);
+}
+
+// Workgroups of the split form: 2048 amplitudes (32 KB) or samples each, at
+// most four per CU; 0 below 2^13.
+static int stat_blocks(uint64_t n, uint64_t n_samples) {
+  const uint64_t most = n > n_samples ? n : n_samples;
+  if (most < (uint64_t(1) << 13)) return 0;
+  const uint64_t b = (most + 2047) / 2048;
+  return (int)(b < 1024 ? b : 1024);
+}
+
+uint64_t batch_stats_workspace(uint64_t n, uint64_t n_samples) {
+  return 32 * (uint64_t)stat_blocks(n, n_samples);
+}
+
 hipError_t launch_batch_stats(const double* amps, uint64_t n, int n_qubits, const uint64_t* samples,
-                              uint64_t n_samples, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_stats, dim3(1), dim3(kStatThreads), 0, s, amps, n,
-                     ldexp(1.0, n_qubits), samples, n_samples, out);
+                              uint64_t n_samples, double* out, void* ws, hipStream_t s) {
+  const double dim = ldexp(1.0, n_qubits);
+  const int blocks = ws ? stat_blocks(n, n_samples) : 0;
+  if (blocks == 0) {
+    hipLaunchKernelGGL(k_batch_stats, dim3(1), dim3(kStatThreads), 0, s, amps, n, dim, samples,
+                       n_samples, out);
+    return hipGetLastError();
+  }
+  double* part = static_cast<double*>(ws);
+  hipLaunchKernelGGL(k_batch_stats_part, dim3((unsigned)blocks), dim3(256), 0, s, amps, n, samples,
+                     n_samples, part);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_batch_stats_sum, dim3(1), dim3(256), 0, s, part, blocks, n, dim, n_samples, out);
   return hipGetLastError();
 }
 
