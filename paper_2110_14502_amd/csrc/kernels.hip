@@ -91,21 +91,37 @@ __global__ void k_slice_sum(const void* root, const int32_t* rexp, int64_t rs, i
   const int jb = (int)(t / n_elems);
   const int jbs = dep_b ? jb : 0;
   double sr = 0.0, si = 0.0;
-  for (int js = 0; js < gs; ++js) {
-    const int jss = dep_s ? js : 0;
-    double vr = 0.0, vi = 0.0;
-    if (!(flags && flags[js])) {
-      const float2 v = load_c<S>(root, jss * rs + jbs * rb + e);
-      const int ex = rexp ? rexp[jss * res + jbs * reb] : 0;
-      vr = ldexp((double)v.x, ex);
-      vi = ldexp((double)v.y, ex);
+  // Eight slices' values, exponents and flags are read together (their
+  // latencies overlap; one slice at a time took 16 us for 32 slices) and added
+  // in slice order.
+  constexpr int B = 8;
+  for (int j0 = 0; j0 < gs; j0 += B) {
+    float2 v[B];
+    int ex[B], skip[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const int js = j0 + i < gs ? j0 + i : gs - 1;
+      const int jss = dep_s ? js : 0;
+      v[i] = load_c<S>(root, jss * rs + jbs * rb + e);
+      ex[i] = rexp ? rexp[jss * res + jbs * reb] : 0;
+      skip[i] = flags ? flags[js] : 0;
     }
-    sr += vr;
-    si += vi;
-    if (per_slice && !(flags && flags[js])) {
-      const int64_t o = (((ps_row0 + js) * n_batch_total + (b0 + jb)) * n_elems + e) * 2;
-      per_slice[o] = vr;
-      per_slice[o + 1] = vi;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const int js = j0 + i;
+      if (js >= gs) break;
+      double vr = 0.0, vi = 0.0;
+      if (!skip[i]) {
+        vr = ldexp((double)v[i].x, ex[i]);
+        vi = ldexp((double)v[i].y, ex[i]);
+      }
+      sr += vr;
+      si += vi;
+      if (per_slice && !skip[i]) {
+        const int64_t o = (((ps_row0 + js) * n_batch_total + (b0 + jb)) * n_elems + e) * 2;
+        per_slice[o] = vr;
+        per_slice[o + 1] = vi;
+      }
     }
   }
   const int64_t o = ((b0 + jb) * (int64_t)n_elems + e) * 2;
