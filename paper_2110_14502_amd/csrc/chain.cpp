@@ -79,7 +79,7 @@ ChainPlan plan_chains(const rqc_plan* p, int prec) {
     ok = ok && !step_lp_store(p, prec, i);
     for (int x : {st.a, st.b}) {
       if (x >= nl) ok = ok && !step_lp_store(p, prec, (size_t)pd.step_of_node[x]);
-      else ok = ok && pd.net.leaves[x].labels.size() <= 8;
+      else ok = ok && (int)pd.net.leaves[x].labels.size() <= kChainLeafBits;
     }
     small[i] = ok;
   }
@@ -103,9 +103,24 @@ ChainPlan plan_chains(const rqc_plan* p, int prec) {
         }
       }
     }
+    // Inputs of at most 16 elements first (the kernel loads them together).
+    std::stable_partition(t.inputs.begin(), t.inputs.end(),
+                          [&](int x) { return pd.layout[(size_t)x].size() <= 4; });
+    // By level: a step comes one level after the later of its operands, so
+    // steps of one level are independent; execution order within.
     std::sort(steps.begin(), steps.end());
+    std::vector<int> level(ns, 0);
+    for (int i : steps)
+      for (int x : {pd.steps[(size_t)i].a, pd.steps[(size_t)i].b}) {
+        const int j = x >= nl ? pd.step_of_node[x] : -1;
+        if (j >= 0 && std::binary_search(steps.begin(), steps.end(), j))
+          level[(size_t)i] = std::max(level[(size_t)i], level[(size_t)j] + 1);
+      }
+    std::stable_sort(steps.begin(), steps.end(),
+                     [&](int x, int y) { return level[(size_t)x] < level[(size_t)y]; });
     t.steps = steps;
-    // Lay the tensors out in execution order; every input is loaded first.
+    // Lay the tensors out in that order; every input is loaded first, and a
+    // level's operands go when the whole level is done.
     Pool pool;
     std::vector<int> at(pd.tree.left.size(), -1), slot(pd.tree.left.size(), -1);
     auto elems = [&](int x) { return ((1 << pd.layout[(size_t)x].size()) + 1) & ~1; };
@@ -116,10 +131,13 @@ ChainPlan plan_chains(const rqc_plan* p, int prec) {
       slot[(size_t)x] = n_slot++;
       t.input_lds.push_back(at[(size_t)x]);
     }
-    for (int i : t.steps) {
+    std::vector<int> done;
+    for (size_t q = 0; q < t.steps.size(); ++q) {
+      const int i = t.steps[q];
       const Step& st = pd.steps[(size_t)i];
       ChainStep c = base[(size_t)i];
       c.m = (uint8_t)st.m, c.n = (uint8_t)st.n, c.k = (uint8_t)st.k;
+      c.tiles = (uint16_t)(1 << (std::max(0, st.m - 4) + std::max(0, st.n - 3)));
       slot[(size_t)st.node] = n_slot++;
       if (i != (int)root) {
         at[(size_t)st.node] = pool.alloc(elems(st.node));
@@ -128,9 +146,14 @@ ChainPlan plan_chains(const rqc_plan* p, int prec) {
       }
       c.lds_a = (uint16_t)at[(size_t)st.a], c.lds_b = (uint16_t)at[(size_t)st.b];
       c.slot_a = (uint16_t)slot[(size_t)st.a], c.slot_b = (uint16_t)slot[(size_t)st.b];
+      done.push_back(st.a);
+      done.push_back(st.b);
+      c.level_end = q + 1 == t.steps.size() || level[(size_t)t.steps[q + 1]] != level[(size_t)i];
+      if (c.level_end) {
+        for (int x : done) pool.release(at[(size_t)x]);
+        done.clear();
+      }
       t.prog.push_back(c);
-      pool.release(at[(size_t)st.a]);
-      pool.release(at[(size_t)st.b]);
     }
     if (peak <= kChainMaxElems && (int)t.steps.size() <= kChainMaxSteps && n_slot <= kChainMaxSlots) {
       out.lds_elems = std::max(out.lds_elems, peak);

@@ -594,6 +594,7 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
     c.dep_s = R.dep_s, c.dep_b = R.dep_b;
     c.input0 = (int32_t)inputs.size(), c.n_inputs = (int32_t)t.inputs.size();
     c.step0 = (int32_t)csteps.size(), c.n_steps = (int32_t)t.prog.size();
+    for (int x : t.inputs) c.n_small += pd.layout[x].size() <= 4;  // sorted: small ones first
     comps.push_back(c);
     csteps.insert(csteps.end(), t.prog.begin(), t.prog.end());
     for (size_t i = 0; i < t.inputs.size(); ++i) {
@@ -607,11 +608,18 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
       in.e_off = P.e_off, in.m_off = P.m_off;
       in.es = P.es, in.eb = P.eb;
       in.leaf = x < nl && !P.resident;
-      in.resident = P.resident;
+      in.resident = P.resident || in.leaf;
       if (in.leaf) {
-        in.src = p->leaf_store_off[x];
-        leaf_pos(x, in.pos);
-        in.nsel = selectors(x, in.sel_pos, in.sel_src);
+        in.src = 8 * p->leaf_store_off[x];
+        int8_t pos[8], sel_pos[8];
+        int16_t sel_src[8];
+        leaf_pos(x, pos);
+        in.nsel = selectors(x, sel_pos, sel_src);
+        for (int b = 0; b < in.rank; ++b) in.pos |= (uint32_t)pos[b] << (8 * b);
+        for (int j = 0; j < in.nsel; ++j) {
+          in.sel_src[j] = sel_src[j];
+          in.sel_pos |= (uint32_t)sel_pos[j] << (8 * j);
+        }
       } else {
         in.src = P.off;
         in.s_stride = P.s_stride, in.b_stride = P.b_stride;

@@ -29,7 +29,7 @@ struct Placement {
 // mode: the subtrees' steps in execution order, their inputs, and where every
 // tensor sits in LDS.  Independent of the group size.
 struct ChainTree {
-  std::vector<int> steps;              // plan steps, the last one makes the root
+  std::vector<int> steps;              // plan steps by level, the last one makes the root
   std::vector<int> inputs;             // tree nodes read from memory
   std::vector<ChainStep> prog;         // per step
   std::vector<int> input_lds;          // per input

@@ -88,35 +88,42 @@ struct LeafJob {
 
 // Fused small subtrees (k_chain.hip): one workgroup evaluates one subtree for
 // one copy with every tensor in LDS.  Limits of one subtree; the tensors
-// share kChainMaxElems complex values of LDS (54 KB, which with the program
+// share kChainMaxElems complex values of LDS (53 KB, which with the program
 // and the scale slots stays below 64 KB).
-constexpr int kChainMaxSteps = 128, kChainMaxSlots = 288, kChainMaxElems = 6912;
+constexpr int kChainMaxSteps = 128, kChainMaxSlots = 288, kChainMaxElems = 6784;
 
 // One input tensor of a subtree: a leaf (bound from the leaf store by the
-// slice's and the bitstring's selector bits) or a computed tensor.
-struct ChainInput {
-  int64_t src;                  // leaf: element offset in the leaf store; else bytes from its region
+// slice's and the bitstring's selector bits; at most kChainLeafBits labels) or
+// a computed tensor.
+constexpr int kChainLeafBits = 4;
+struct alignas(16) ChainInput {
+  int64_t src;                  // bytes from the region's base
+  int32_t resident, lds;        // region: resident memory (leaf store) or arena; LDS element
+  int32_t rank, leaf;           // 2^rank elements
+  float max_const;
+  uint32_t pos;                 // leaf: address bit of element bit i in byte i
+  int16_t sel_src[4];           // leaf: as in LeafJob
+  uint32_t sel_pos;             // leaf: address bit of selector i in byte i
+  int32_t nsel;
   int64_t s_stride, b_stride;   // copy strides, elements
   int64_t e_off, m_off;         // bytes of the scale arrays in its region (-1: none)
   int32_t es, eb;               // copy strides of the scale arrays
-  int32_t leaf, resident;       // region: the plan's resident memory or the call's arena
-  int32_t rank, lds;            // 2^rank elements at LDS element lds
-  int32_t nsel;                 // leaf: as in LeafJob
-  float max_const;
-  int8_t pos[8], sel_pos[8];
-  int16_t sel_src[8];
+  int32_t pad[2];
 };
+static_assert(sizeof(ChainInput) == 96, "read as 16-byte words");
 
 // One step of a subtree: tensors at LDS elements lds_*, scale slots (inputs
 // first, then the steps in order); rpos / cpos: address bit in C of row /
-// column bit i (0 past the step's own).
-struct ChainStep {
-  uint16_t lds_a, lds_b, lds_c, slot_a, slot_b;
-  uint8_t m, n, k, pad;
+// column bit i (0 past the step's own); tiles: 16 x 8 output tiles;
+// level_end: the steps up to here and after the previous such mark do not
+// depend on each other.
+struct alignas(16) ChainStep {
+  uint16_t lds_a, lds_b, lds_c, slot_a, slot_b, tiles;
+  uint8_t m, n, k, level_end;
   int8_t rpos[12], cpos[12];
-  uint16_t pad2;
+  uint16_t pad[4];
 };
-static_assert(sizeof(ChainStep) == 40, "copied as words");
+static_assert(sizeof(ChainStep) == 48, "copied as words");
 
 // One subtree: its program and where its root goes (arena bytes, copy
 // strides in elements, scale arrays).
@@ -124,6 +131,7 @@ struct ChainComp {
   int64_t dst, s_stride, b_stride, e_off, m_off;
   int32_t es, eb, dep_s, dep_b;
   int32_t input0, n_inputs, step0, n_steps;
+  int32_t n_small, pad;         // the first n_small inputs hold at most 16 elements
 };
 
 struct ChainArgs {
