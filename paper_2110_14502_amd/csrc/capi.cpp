@@ -299,6 +299,7 @@ rqc_status rqc_plan_set_group_limit(rqc_plan* p, int32_t max_slices, int32_t max
   if (max_slices < 0 || max_bits < 0) throw rqc::Error{RQC_EINVAL, "negative group limit"};
   p->group_limit_s = max_slices;
   p->group_limit_b = max_bits;
+  p->groups.clear();
   return RQC_OK;
   RQC_CATCH
 }

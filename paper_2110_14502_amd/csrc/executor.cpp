@@ -332,6 +332,7 @@ void select_steps(rqc_plan* p) {
     p->chain[m] = plan_chains(p, m);
   }
   p->layouts.clear();
+  p->groups.clear();
   clear_graphs(p);
 }
 
@@ -653,15 +654,16 @@ WsLayout ws_layout(rqc_plan* p, const GroupLayout& L, uint64_t n_ids, uint64_t n
   const PlanData& pd = p->pd;
   WsLayout w;
   int64_t o = 0;
+  // The call's inputs first, back to back (one upload).
   w.ids_off = o;
   o = align256(o + 8 * (int64_t)n_ids);
   w.bits_off = o;
   o = align256(o + (int64_t)n_batch * (int64_t)std::max<size_t>(1, pd.net.closed.size()));
+  w.jobs_off = o;
+  o = align256(o + (int64_t)L.blob.size());
   w.n_bgroups = ((int64_t)n_batch + L.gb - 1) / L.gb;
   w.flags_off = o;
   o = align256(o + 4 * (int64_t)n_ids * w.n_bgroups);
-  w.jobs_off = o;
-  o = align256(o + (int64_t)L.blob.size());
   w.tmp_off = o;
   o = align256(o + 16 * (int64_t)n_batch * (int64_t(1) << pd.net.open.size()));
   w.scale_off = o;
@@ -851,14 +853,36 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
   }
 }
 
+// One copy of the call's inputs (slice ids, closed bits, device program) to
+// the start of its workspace: each copy of its own costs the stream 8-10 us.
+void upload_inputs(const GroupLayout& L, const WsLayout& W, char* ws, const uint64_t* ids,
+                   uint64_t n_ids, const std::vector<uint8_t>& bits, std::vector<char>& host,
+                   hipStream_t s) {
+  host.assign((size_t)(W.jobs_off + (int64_t)L.blob.size()), 0);
+  std::memcpy(host.data() + W.ids_off, ids, 8 * n_ids);
+  std::memcpy(host.data() + W.bits_off, bits.data(), bits.size());
+  if (!L.blob.empty()) std::memcpy(host.data() + W.jobs_off, L.blob.data(), L.blob.size());
+  hip_check(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, s), "call inputs");
+}
+
 bool fits(rqc_plan* p, int prec, int gs, int gb, uint64_t n_ids, uint64_t n_batch,
           size_t ws_bytes) {
   GroupLayout L = compute_layout(p, prec, gs, gb);
   return (size_t)ws_layout(p, L, n_ids, n_batch).total <= ws_bytes;
 }
 
+// Trying a group size lays the whole call out (50-150 us of host time each, a
+// dozen tries), so the sizes found are kept per call shape until the steps'
+// kernels or the group limits change.
 void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_t ws_bytes,
                   int& gs, int& gb) {
+  const auto key = std::make_tuple(prec, n_ids, n_batch, ws_bytes);
+  const auto hit = p->groups.find(key);
+  if (hit != p->groups.end()) {
+    gs = hit->second.first;
+    gb = hit->second.second;
+    return;
+  }
   int max_gs = (int)std::min<uint64_t>(n_ids, 4096);
   int max_gb = (int)std::min<uint64_t>(n_batch, 4096);
   if (p->group_limit_s > 0) max_gs = std::min(max_gs, p->group_limit_s);
@@ -878,6 +902,8 @@ void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_
     else hi = mid - 1;
   }
   gs = lo;
+  if (p->groups.size() >= 64) p->groups.clear();
+  p->groups[key] = {gs, gb};
 }
 
 void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t* bits,
@@ -916,11 +942,7 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
   const GroupLayout& L = group_layout(p, prec, gs, gb);
   const WsLayout W = ws_layout(p, L, n_ids, n_batch);
   char* ws = static_cast<char*>(ws_v);
-  hip_check(hipMemcpyAsync(ws + W.ids_off, ids.data(), 8 * n_ids, hipMemcpyHostToDevice, s), "ids");
-  hip_check(hipMemcpyAsync(ws + W.bits_off, b.data(), b.size(), hipMemcpyHostToDevice, s), "bits");
-  if (!L.blob.empty())
-    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s),
-              "program");
+  upload_inputs(L, W, ws, ids.data(), n_ids, b, r.staging, s);
   GraphKey key{prec, gs, gb, n_ids, n_batch, ws_v, out, per_slice};
   auto it = p->graphs.find(key);
   int reused = 0;
@@ -978,6 +1000,7 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
   r.n_batch = n_batch;
   r.ids = ids;
   r.bits = b;
+  r.stream = s;
   r.ws = ws;
   r.ws_bytes = ws_bytes;
   r.out = out;
@@ -990,8 +1013,29 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
 
 void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool sync) {
   std::memset(rep, 0, sizeof *rep);
-  if (sync) hip_check(hipStreamSynchronize(s), "synchronize");
-  if (!r.active) return;
+  if (!r.active) {
+    if (sync) hip_check(hipStreamSynchronize(s), "synchronize");
+    return;
+  }
+  const GroupLayout& L0 = group_layout(p, r.prec, r.gs, r.gb);
+  const WsLayout W0 = ws_layout(p, L0, r.n_ids, r.n_batch);
+  const int64_t nbg = W0.n_bgroups;
+  std::vector<int32_t> flags((size_t)(r.n_ids * nbg));
+  if (sync && s == r.stream && flags.size() <= kPinnedFlags) {
+    // The flags follow the call on its stream, so that one wait covers both
+    // (a blocking copy after the wait takes another 20 us).
+    if (!p->pinned_flags)
+      hip_check(hipHostMalloc(reinterpret_cast<void**>(&p->pinned_flags), 4 * kPinnedFlags), "flag buffer");
+    hip_check(hipMemcpyAsync(p->pinned_flags, r.ws + W0.flags_off, 4 * flags.size(),
+                             hipMemcpyDeviceToHost, s),
+              "flags");
+    hip_check(hipStreamSynchronize(s), "synchronize");
+    std::memcpy(flags.data(), p->pinned_flags, 4 * flags.size());
+  } else {
+    if (sync) hip_check(hipStreamSynchronize(s), "synchronize");
+    hip_check(hipMemcpy(flags.data(), r.ws + W0.flags_off, 4 * flags.size(), hipMemcpyDeviceToHost),
+              "flags");
+  }
   p->last_timing = rqc_timing{};
   p->tms.clear();
   for (size_t i = 0; i < p->trec.size() && p->timing_kernel >= 0; ++i) {
@@ -1008,12 +1052,6 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
   rep->bits_per_group = r.gb;
   rep->graph_reused = r.graph_reused;
   rep->flops = r.flops;
-  const GroupLayout& L0 = group_layout(p, r.prec, r.gs, r.gb);
-  const WsLayout W0 = ws_layout(p, L0, r.n_ids, r.n_batch);
-  const int64_t nbg = W0.n_bgroups;
-  std::vector<int32_t> flags((size_t)(r.n_ids * nbg));
-  hip_check(hipMemcpy(flags.data(), r.ws + W0.flags_off, 4 * flags.size(), hipMemcpyDeviceToHost),
-            "flags");
   // A slice is re-run when any of its bitstring groups was flagged; its FP32
   // result is then added for exactly those groups, whose slice sums skipped it.
   std::vector<uint64_t> redo;
@@ -1042,12 +1080,7 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
   std::vector<int32_t> f32_flags((size_t)W.n_bgroups);
   for (uint64_t idx : redo) {
     const uint64_t id = r.ids[idx];
-    hip_check(hipMemcpyAsync(r.ws + W.ids_off, &id, 8, hipMemcpyHostToDevice, s), "ids");
-    hip_check(hipMemcpyAsync(r.ws + W.bits_off, r.bits.data(), r.bits.size(), hipMemcpyHostToDevice, s), "bits");
-    if (!L.blob.empty())
-      hip_check(hipMemcpyAsync(r.ws + W.jobs_off, L.blob.data(), L.blob.size(),
-                               hipMemcpyHostToDevice, s),
-                "program");
+    upload_inputs(L, W, r.ws, &id, 1, r.bits, r.staging, s);
     record_call(p, L, W, 1, r.n_batch, r.ws, tmp, nullptr, 0, s);
     for (int64_t g = 0; g < nbg; ++g) {
       if (!flags[(size_t)(g * (int64_t)r.n_ids + (int64_t)idx)]) continue;
@@ -1079,5 +1112,6 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
 rqc_plan::~rqc_plan() {
   rqc::clear_graphs(this);
   for (auto e : tev) (void)hipEventDestroy(e);
+  if (pinned_flags) (void)hipHostFree(pinned_flags);
   if (capture_stream) (void)hipStreamDestroy(capture_stream);
 }

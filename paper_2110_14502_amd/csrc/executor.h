@@ -74,6 +74,8 @@ struct PendingRun {
   uint64_t n_ids = 0, n_batch = 0;
   std::vector<uint64_t> ids;
   std::vector<uint8_t> bits;
+  std::vector<char> staging;   // the uploaded inputs
+  hipStream_t stream = nullptr;
   char* ws = nullptr;
   size_t ws_bytes = 0;
   double* out = nullptr;
@@ -90,6 +92,10 @@ struct WsLayout {
   int64_t ids_off, bits_off, flags_off, jobs_off, tmp_off, scale_off, arena_off, total;
   int64_t n_bgroups;
 };
+
+// Words of the pinned buffer the flags of a call are read through (64 KB; a
+// call with more flags reads them with a blocking copy).
+constexpr size_t kPinnedFlags = 16384;
 
 // A captured call and the event recorded after its last launch (an exec is
 // destroyed only once that event has completed).
@@ -143,10 +149,12 @@ struct rqc_plan {
   rqc_timing last_timing{};
   // Caches.
   std::map<std::tuple<int, int, int>, rqc::GroupLayout> layouts;
+  std::map<std::tuple<int, uint64_t, uint64_t, size_t>, std::pair<int, int>> groups;
   std::map<rqc::GraphKey, rqc::GraphEntry> graphs;
   uint64_t graph_clock = 0;
   hipStream_t capture_stream = nullptr;
   rqc::PendingRun pending;
+  int32_t* pinned_flags = nullptr;      // kPinnedFlags words the report reads flags through
   ~rqc_plan();
 };
 
@@ -168,6 +176,11 @@ void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_
                   int& gs, int& gb);
 bool fits(rqc_plan* p, int prec, int gs, int gb, uint64_t n_ids, uint64_t n_batch,
           size_t ws_bytes);
+// Slice ids, closed bits and the device program to the call's workspace,
+// through `host` (kept by the caller while the copy may read it).
+void upload_inputs(const GroupLayout& L, const WsLayout& W, char* ws, const uint64_t* ids,
+                   uint64_t n_ids, const std::vector<uint8_t>& bits, std::vector<char>& host,
+                   hipStream_t s);
 
 // Every launch of one call (ids, bits and the device program already in the
 // workspace), in order on `s`.

@@ -97,16 +97,6 @@ std::vector<std::pair<int, int>> candidates(rqc_plan* p, int m, size_t i) {
   return c;
 }
 
-void copy_call_inputs(rqc_plan* p, const GroupLayout& L, const WsLayout& W, char* ws,
-                      const std::vector<uint64_t>& ids, const std::vector<uint8_t>& bits,
-                      hipStream_t s) {
-  hip_check(hipMemcpyAsync(ws + W.ids_off, ids.data(), 8 * ids.size(), hipMemcpyHostToDevice, s), "ids");
-  hip_check(hipMemcpyAsync(ws + W.bits_off, bits.data(), bits.size(), hipMemcpyHostToDevice, s), "bits");
-  if (!L.blob.empty())
-    hip_check(hipMemcpyAsync(ws + W.jobs_off, L.blob.data(), L.blob.size(), hipMemcpyHostToDevice, s),
-              "program");
-}
-
 struct Events {
   hipEvent_t a = nullptr, b = nullptr;
   Events() {
@@ -155,7 +145,8 @@ void autotune(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, void* ws_
   std::vector<uint64_t> ids(gs);
   for (int i = 0; i < gs; ++i) ids[i] = (uint64_t)i;
   std::vector<uint8_t> bits((size_t)gb * std::max<size_t>(1, pd.net.closed.size()), 0);
-  copy_call_inputs(p, L, W, ws, ids, bits, s);
+  std::vector<char> staging;
+  upload_inputs(L, W, ws, ids.data(), ids.size(), bits, staging, s);
   double* out = reinterpret_cast<double*>(ws + W.tmp_off);
   record_call(p, L, W, (uint64_t)gs, (uint64_t)gb, ws, out, nullptr, 0, s);
   hip_check(hipStreamSynchronize(s), "tuning warm-up");
