@@ -555,9 +555,10 @@ def pair_workspace_bytes(labels_a, labels_b, labels_c, kernel=-1, batch=1, strid
 def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, batch=1,
                   stride_a=0, stride_b=0, stride_c=0, prec=F32, stream=None, workspace=None):
     """C = A * B summed over shared labels (complex64 torch tensors on
-    device).  A 16-bit call with a long sum takes the two-phase form and
-    needs a device workspace (pair_workspace_bytes); one is allocated with
-    torch unless `workspace` (a uint8 device tensor) is given."""
+    device).  A call with a long sum takes a two-phase form and needs a
+    device workspace (pair_workspace_bytes); one is allocated with torch
+    unless `workspace` (a uint8 device tensor) is given.  An FP32 call for
+    which no workspace can be allocated runs without one."""
     import torch
     prec = PRECISIONS.get(prec, prec) if isinstance(prec, str) else int(prec)
     if C_out is None:
@@ -567,7 +568,12 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
                                 prec)
     if need:
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
+            try:
+                workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
+            except torch.OutOfMemoryError:
+                if prec != F32:
+                    raise
+    if need and workspace is not None:
         _check(_lib.rqc_pair_contract_ws(_i32(labels_a), len(labels_a), _i32(labels_b),
                                          len(labels_b), _i32(labels_c), len(labels_c), _ptr(A),
                                          _ptr(B), _ptr(C_out), int(batch), int(stride_a),

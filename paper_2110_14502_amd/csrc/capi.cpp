@@ -461,6 +461,65 @@ Gemm16Shape gemm16_shape(const std::vector<int>& la, const std::vector<int>& lb,
   return g;
 }
 
+// FP32 long sums on the FP16 matrix cores (k_split32.hip), automatic kernel
+// choice only.  Taken when the output has at least one 256 x 128 tile (either
+// operand on the row side) and the sum 2^10 terms or more, or 2^8 and the
+// product 2^34 multiply-adds or more.  The FP32 kernel takes 0.15 us per summed
+// term for each round of 512 tiles; this form 90-100 us for its six launches
+// and then a third of the FP32 time: (m, n, k) = (8, 7, 10) 161 -> 96 us, (15,
+// 8, 10) 507 -> 489, (12, 12, 12) 3.70 -> 1.53 ms, (14, 13, 9) 4.31 -> 2.17;
+// below the line (14, 8, 9) 144 -> 158 us, (12, 12, 8) 310 -> 366.
+// Workspaces above 24 GiB (12 bytes per operand element) stay with the FP32
+// kernel, so that the largest steps (rank 32) still fit beside their operands,
+// and so do batches above 64 (the copies run one after the other).
+constexpr int kSplit32MinK = 10, kSplit32ShortK = 8, kSplit32ShortWork = 34;
+constexpr uint64_t kSplit32MaxBytes = uint64_t(24) << 30;
+struct Split32Shape {
+  int m = -1, n = 0, k = 0, ksplit = 0;
+  bool swap = false;               // B's free indices on the row side
+  std::vector<int> Mf, Nf, K;      // row, column and summed labels
+  uint64_t hdr = 0, bytes_a = 0, bytes_b = 0, bytes_p = 0;
+  uint64_t total() const { return hdr + bytes_a + bytes_b + bytes_p; }
+};
+
+Split32Shape split32_shape(const std::vector<int>& la, const std::vector<int>& lb,
+                           const std::vector<int>& lc, int32_t batch, int32_t kernel, int32_t prec) {
+  Split32Shape g;
+  if (prec != RQC_F32 || kernel != -1 || batch > 64) return g;
+  int shared = 0;  // most calls end here
+  for (int x : la) shared += std::find(lb.begin(), lb.end(), x) != lb.end();
+  if (shared < kSplit32ShortK) return g;
+  for (int x : la) (std::find(lb.begin(), lb.end(), x) != lb.end() ? g.K : g.Mf).push_back(x);
+  for (int x : lb)
+    if (std::find(la.begin(), la.end(), x) == la.end()) g.Nf.push_back(x);
+  g.swap = g.Nf.size() > g.Mf.size();
+  if (g.swap) std::swap(g.Mf, g.Nf);
+  const int m = (int)g.Mf.size(), n = (int)g.Nf.size(), k = (int)g.K.size();
+  if (m < 8 || n < 7 || k > 24) return g;
+  if (k < kSplit32MinK && (k < kSplit32ShortK || m + n + k < kSplit32ShortWork)) return g;
+  if (m + k > 36 || n + k > 36 || m + n > 36) return g;
+  auto c_order = [&](std::vector<int>& v) {
+    std::stable_sort(v.begin(), v.end(), [&](int x, int y) {
+      return std::find(lc.begin(), lc.end(), x) < std::find(lc.begin(), lc.end(), y);
+    });
+  };
+  c_order(g.Mf);
+  c_order(g.Nf);
+  g.hdr = 256 + 8 * rqc::kSplitParts;  // header, then the partial maxima of A and of B
+  g.bytes_a = uint64_t(12) << (m + k);
+  g.bytes_b = uint64_t(12) << (n + k);
+  // Split the sum while the tiles cannot fill the GPU (one workgroup per CU),
+  // keeping at least 16 chunks of 32 terms per split.
+  const uint64_t tiles = uint64_t(1) << (m - 8 + n - 7);
+  while ((tiles << g.ksplit) < 512 && k - 5 - g.ksplit > 4) ++g.ksplit;
+  if (g.ksplit) g.bytes_p = uint64_t(8) << (m + n + g.ksplit);
+  if (g.total() > kSplit32MaxBytes) return g;
+  g.m = m;
+  g.n = n;
+  g.k = k;
+  return g;
+}
+
 // Split sum of an FP32 call on the generic kernel whose output tiles cannot
 // fill the GPU (as the planner's layouts split plan steps): 2^ks workgroups
 // per output tile, each summing a contiguous range of the summed indices into
@@ -499,6 +558,74 @@ std::vector<int8_t> perm_sources(const std::vector<int>& in, const std::vector<i
   return src;
 }
 
+// An FP32 call with a long sum (shape g): per copy the operands' maxima and
+// packing (a shared operand once), the GEMM, and the FP32 kernel, which runs
+// only if an operand was flagged.
+void pair_split32(const Split32Shape& g, const std::vector<int>& la, const std::vector<int>& lb,
+                  const std::vector<int>& lc, const void* A, const void* B, void* C, int32_t batch,
+                  int64_t stride_a, int64_t stride_b, int64_t stride_c, char* ws, hipStream_t s) {
+  // Fragment order, lowest bit first: terms 0-2, rows 0-4, terms 3.., rows 5..
+  auto sources = [&](const std::vector<int>& in, const std::vector<int>& free_labels) {
+    const int nf = (int)free_labels.size();
+    std::vector<int> out;  // lowest bit first
+    auto row = [&](int i) { return free_labels[nf - 1 - i]; };
+    auto term = [&](int i) { return g.K[g.k - 1 - i]; };
+    for (int i = 0; i < 3; ++i) out.push_back(term(i));
+    for (int i = 0; i < 5; ++i) out.push_back(row(i));
+    for (int i = 3; i < g.k; ++i) out.push_back(term(i));
+    for (int i = 5; i < nf; ++i) out.push_back(row(i));
+    std::reverse(out.begin(), out.end());
+    return perm_sources(in, out);
+  };
+  const std::vector<int>&lr = g.swap ? lb : la, &lcl = g.swap ? la : lb;  // row and column operand
+  const std::vector<int8_t> src_r = sources(lr, g.Mf), src_c = sources(lcl, g.Nf);
+  rqc::SplitHdr* hdr = reinterpret_cast<rqc::SplitHdr*>(ws);
+  uint32_t* part_r = reinterpret_cast<uint32_t*>(ws + 256);
+  uint32_t* part_c = part_r + rqc::kSplitParts;
+  rqc::SplitDesc d{};
+  d.A = ws + g.hdr;
+  d.B = d.A + g.bytes_a;
+  d.hdr = hdr;
+  d.plane_a = (int64_t)(g.bytes_a / 3);
+  d.plane_b = (int64_t)(g.bytes_b / 3);
+  d.m = g.m, d.n = g.n, d.k = g.k;
+  d.ksplit = g.ksplit;
+  d.P = g.ksplit ? reinterpret_cast<float2*>(ws + g.hdr + g.bytes_a + g.bytes_b) : nullptr;
+  const int rank_c = (int)lc.size();
+  auto c_bit = [&](int label) {
+    return (int8_t)(rank_c - 1 - (std::find(lc.begin(), lc.end(), label) - lc.begin()));
+  };
+  for (int b = 0; b < g.m; ++b) d.crow[b] = c_bit(g.Mf[g.m - 1 - b]);
+  for (int b = 0; b < g.n; ++b) d.ccol[b] = c_bit(g.Nf[g.n - 1 - b]);
+  int kern = rqc::KERN_MFMA;
+  rqc::StepDesc f = rqc::make_pair_desc(la, lb, lc, kern);
+  f.variant = rqc::kVarPersistent;
+  f.run_if = hdr;
+  for (int32_t j = 0; j < batch; ++j) {
+    const float2* a = static_cast<const float2*>(A) + j * stride_a;
+    const float2* b = static_cast<const float2*>(B) + j * stride_b;
+    float2* c = static_cast<float2*>(C) + j * stride_c;
+    const int64_t stride_r = g.swap ? stride_b : stride_a, stride_l = g.swap ? stride_a : stride_b;
+    if (j == 0 || stride_r)
+      rqc::hip_check(rqc::launch_split_pack(g.swap ? b : a, const_cast<char*>(d.A), (int)lr.size(),
+                                            src_r.data(), d.plane_a, false, part_r, &hdr->flag_a,
+                                            &hdr->exp_a, s),
+                     "pack rows");
+    if (j == 0 || stride_l)
+      rqc::hip_check(rqc::launch_split_pack(g.swap ? a : b, const_cast<char*>(d.B), (int)lcl.size(),
+                                            src_c.data(), d.plane_b, true, part_c, &hdr->flag_b,
+                                            &hdr->exp_b, s),
+                     "pack columns");
+    d.C = c;
+    rqc::hip_check(rqc::launch_split_gemm(d, s), "split FP32 GEMM");
+    f.A = a;
+    f.B = b;
+    f.C = c;
+    rqc::hip_check(rqc::launch_step(f, kern, rqc::ST_C64, rqc::ST_C64, rqc::ST_C64, 0, s),
+                   "FP32 kernel for wide ranges");
+  }
+}
+
 // Labels of a pairwise call, validated (ranks, NULLs, repeats, batch).
 void pair_labels(const int32_t* labels_a, int32_t rank_a, const int32_t* labels_b, int32_t rank_b,
                  const int32_t* labels_c, int32_t rank_c, int32_t batch_count, std::vector<int>& la,
@@ -532,7 +659,10 @@ rqc_status rqc_pair_workspace_bytes(const int32_t* labels_a, int32_t rank_a,
   std::vector<int> la, lb, lc;
   pair_labels(labels_a, rank_a, labels_b, rank_b, labels_c, rank_c, batch_count, la, lb, lc);
   const Gemm16Shape g = gemm16_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
-  *bytes = g.m >= 0 ? g.total() : simt_split(la, lb, lc, batch_count, kernel, prec).bytes;
+  const Split32Shape h = split32_shape(la, lb, lc, batch_count, kernel, prec);
+  *bytes = g.m >= 0   ? g.total()
+           : h.m >= 0 ? h.total()
+                      : simt_split(la, lb, lc, batch_count, kernel, prec).bytes;
   return RQC_OK;
   RQC_CATCH
 }
@@ -547,6 +677,16 @@ rqc_status rqc_pair_contract_ws(const int32_t* labels_a, int32_t rank_a, const i
   std::vector<int> la, lb, lc;
   pair_labels(labels_a, rank_a, labels_b, rank_b, labels_c, rank_c, batch_count, la, lb, lc);
   const Gemm16Shape g = gemm16_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
+  const Split32Shape h = split32_shape(la, lb, lc, batch_count, kernel, prec);
+  // Operands and workspace as the packing needs them; the FP32 kernel runs
+  // without a workspace, so a call that brings none (or less) still runs.
+  if (h.m >= 0 && A && B && C && workspace && ws_bytes >= h.total() && (uintptr_t)workspace % 256 == 0 &&
+      ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && stride_a % 2 == 0 && stride_b % 2 == 0 &&
+      (batch_count == 1 || stride_c >= ((int64_t)1 << rank_c))) {
+    pair_split32(h, la, lb, lc, A, B, C, batch_count, stride_a, stride_b, stride_c,
+                 static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
+    return RQC_OK;
+  }
   if (g.m < 0) {
     const SimtSplit sp = simt_split(la, lb, lc, batch_count, kernel, prec);
     if (sp.ks == 0 || (batch_count > 1 && stride_c != ((int64_t)1 << rank_c)))

@@ -295,14 +295,15 @@ hipError_t launch_gemm16(const Gemm16Desc& d, int lp_kind, hipStream_t s) {
     hipLaunchKernelGGL(k_gemm16<ST_BF16>, dim3((unsigned)tiles), dim3(512), 0, s, d);
   else
     return hipErrorInvalidValue;
-  if (d.ksplit) {
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint64_t total = (uint64_t)d.copies << (d.m + d.n);
-    const uint64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(k_gemm16_reduce, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256),
-                       0, s, d);
-  }
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !d.ksplit ? e : launch_gemm16_reduce(d, s);
+}
+
+hipError_t launch_gemm16_reduce(const Gemm16Desc& d, hipStream_t s) {
+  const uint64_t total = (uint64_t)d.copies << (d.m + d.n);
+  const uint64_t blocks = (total + 255) / 256;
+  hipLaunchKernelGGL(k_gemm16_reduce, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
+                     s, d);
   return hipGetLastError();
 }
 

@@ -167,6 +167,7 @@ __global__ __launch_bounds__(256, 2) void k_mfma32(StepDesc d, uint64_t n_items)
   float* Abuf = lds;                                      // [2][kTK][2][kAPlane], pair stride
   float2* Bbuf = reinterpret_cast<float2*>(lds + kABuf);  // [2][kTK][kBStride], pair stride
   float* red = lds + kPersFloats;
+  if (d.run_if && !(d.run_if->flag_a | d.run_if->flag_b)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 

@@ -23,6 +23,13 @@ struct TileMap {
   int8_t cbit[kMaxTile];  // bit inside that role's tile index
 };
 
+// FP32 long sums on the FP16 matrix cores (k_split32.hip): start of the
+// workspace.  flag_*: the operand needs the FP32 kernel; exp_*: power-of-two
+// scales of the packed operands.
+struct SplitHdr {
+  int32_t flag_a, flag_b, exp_a, exp_b;
+};
+
 // One pairwise contraction C[m,n] = sum_k A[m,k] B[k,n] with every index of
 // dimension 2 and arbitrary bit layouts (the permutation is folded into the
 // tile loads and the store, Section 5.4).  `copies` independent problems run
@@ -40,6 +47,7 @@ struct StepDesc {
   const float* maxB;
   float* maxC;
   int32_t* flag;  // per slice (js) non-finite flag, may be null
+  const SplitHdr* run_if;  // FP32 matrix-core kernel: return unless an operand is flagged; may be null
   float maxA_const, maxB_const;
   int64_t sA_s, sA_b, sB_s, sB_b, sC_s, sC_b;  // copy strides, elements
   int32_t eA_s, eA_b, eB_s, eB_b, eC_s, eC_b;  // copy strides, scale arrays
@@ -228,6 +236,33 @@ struct Gemm16Desc {
   int8_t ccol[40];
 };
 hipError_t launch_gemm16(const Gemm16Desc& d, int lp_kind, hipStream_t s);
+// C = the partials of a split sum added in split order (also used by the FP32
+// split-halves GEMM).
+hipError_t launch_gemm16_reduce(const Gemm16Desc& d, hipStream_t s);
+
+// FP32 long sums on the FP16 matrix cores (k_split32.hip).  A and B packed as
+// fragments of FP16 halves, three planes of plane_a / plane_b bytes (12 bytes
+// per element in all); element (row, column) of C as in Gemm16Desc.
+constexpr int kSplitM = 256, kSplitN = 128;  // output tile
+constexpr int kSplitParts = 1024;            // partial maxima per operand
+struct SplitDesc {
+  const char* A;
+  const char* B;
+  void* C;
+  const SplitHdr* hdr;
+  int64_t plane_a, plane_b;
+  int32_t m, n, k;     // bits: rows (>= 8), columns (>= 7), summed (6..24)
+  int32_t ksplit;      // the sum split 2^ksplit ways (partials in P, then reduced)
+  float2* P;           // partials [split][row][column]
+  int8_t crow[40];
+  int8_t ccol[40];
+};
+// Largest components, then packing, of one operand: rank bits, src_of_out the
+// permutation into fragment order, `right` for B.
+hipError_t launch_split_pack(const void* in, char* out, int rank, const int8_t* src_of_out,
+                             int64_t plane, bool right, uint32_t* part, int32_t* flag,
+                             int32_t* scale_exp, hipStream_t s);
+hipError_t launch_split_gemm(const SplitDesc& d, hipStream_t s);
 hipError_t launch_cgemm(int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
                         hipStream_t s);
 

@@ -1,7 +1,7 @@
 // Step dispatch and the small kernels of the path: slice / bitstring
 // instantiation of the leaves (Section 5.1), the FP64 cross-slice reduction
 // (Section 6.4), fills, and the unfused permute used as a baseline.
-#include "kernels_dev.h"
+#include "permute_tiles.h"
 
 namespace rqc {
 
@@ -337,108 +337,12 @@ __global__ __launch_bounds__(256) void k_permute(const float2* in, void* out, Pe
   }
 }
 
-constexpr int kPermBits = 12;                              // tile bits
-constexpr int kPermGroups = (1 << kPermBits) / (4 * 256);  // groups of four elements per thread
-struct PermTiles {
-  int32_t n_outer;
-  int8_t tin[kPermBits];    // input address bit of read-order bit i (ascending)
-  int8_t slot[kPermBits];   // output-order bit of read-order bit i
-  int8_t tout[kPermBits];   // output address bit of output-order bit i (ascending)
-  int8_t oin[48], oout[48]; // input / output address bit of outer bit i
-};
-
-// LDS element of output-order index s: two elements of padding per 32.
-__device__ __forceinline__ int perm_pad(int s) { return s + 2 * (s >> 5); }
-
 template <int OUT>
 __global__ __launch_bounds__(256) void k_permute_tiles(const float2* in, void* out, PermTiles p,
                                                        uint32_t n_iter) {
-  __shared__ __attribute__((aligned(16))) float2 tile[(1 << kPermBits) + 2 * (1 << (kPermBits - 5))];
-  __shared__ int64_t step_in[32], step_out[32];
-  const int tid = threadIdx.x;
-  // Tile of iteration i: outer bits blockIdx.x + gridDim.x * i (the grid is a
-  // power of two); i -> i + 1 moves the bases by step[ctz(i + 1)].
-  const int gbits = 31 - __clz((int)gridDim.x);
-  if (tid < p.n_outer - gbits) {
-    int64_t si = int64_t(1) << p.oin[gbits + tid], so = int64_t(1) << p.oout[gbits + tid];
-    for (int j = 0; j < tid; ++j) {
-      si -= int64_t(1) << p.oin[gbits + j];
-      so -= int64_t(1) << p.oout[gbits + j];
-    }
-    step_in[tid] = si;
-    step_out[tid] = so;
-  }
-  int64_t base_in = 0, base_out = 0;
-  for (int b = 0; b < gbits; ++b)
-    if ((blockIdx.x >> b) & 1u) {
-      base_in += int64_t(1) << p.oin[b];
-      base_out += int64_t(1) << p.oout[b];
-    }
-  // Group g of this thread: read-order elements 4 (tid + 256 g) .. + 3, and
-  // the same indices in output order.
-  int64_t off_in = 0, off_out = 0;
-  int slot_t = 0;
-#pragma unroll
-  for (int b = 0; b < 8; ++b)
-    if ((tid >> b) & 1) {
-      off_in += int64_t(1) << p.tin[2 + b];
-      off_out += int64_t(1) << p.tout[2 + b];
-      slot_t += perm_pad(1 << p.slot[2 + b]);
-    }
-  int64_t gin[kPermGroups], gout[kPermGroups];
-  int gslot[kPermGroups], eslot[4];
-#pragma unroll
-  for (int g = 0; g < kPermGroups; ++g) {
-    gin[g] = gout[g] = 0;
-    gslot[g] = 0;
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-      if ((g >> b) & 1) {
-        gin[g] += int64_t(1) << p.tin[10 + b];
-        gout[g] += int64_t(1) << p.tout[10 + b];
-        gslot[g] += perm_pad(1 << p.slot[10 + b]);
-      }
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    eslot[e] = ((e & 1) ? perm_pad(1 << p.slot[0]) : 0) + ((e & 2) ? perm_pad(1 << p.slot[1]) : 0);
-  float4 v[kPermGroups][2];
-  auto load = [&]() {
-#pragma unroll
-    for (int g = 0; g < kPermGroups; ++g) {
-      const float4* src = reinterpret_cast<const float4*>(in + base_in + off_in + gin[g]);
-      v[g][0] = src[0];
-      v[g][1] = src[1];
-    }
-  };
-  load();
-  __syncthreads();
-  for (uint32_t i = 0; i < n_iter; ++i) {
-#pragma unroll
-    for (int g = 0; g < kPermGroups; ++g) {
-      const int s = slot_t + gslot[g];
-      tile[s + eslot[0]] = make_float2(v[g][0].x, v[g][0].y);
-      tile[s + eslot[1]] = make_float2(v[g][0].z, v[g][0].w);
-      tile[s + eslot[2]] = make_float2(v[g][1].x, v[g][1].y);
-      tile[s + eslot[3]] = make_float2(v[g][1].z, v[g][1].w);
-    }
-    __syncthreads();
-    const int64_t bo = base_out + off_out;
-    if (i + 1 < n_iter) {
-      const int b = __builtin_ctz(i + 1);
-      base_in += step_in[b];
-      base_out += step_out[b];
-      load();
-    }
-#pragma unroll
-    for (int g = 0; g < kPermGroups; ++g) {
-      const float4* src = reinterpret_cast<const float4*>(tile + perm_pad(4 * (tid + 256 * g)));
-      const float4 a = src[0], c = src[1];
-      put_elem4<OUT>(out, bo + gout[g], make_float2(a.x, a.y), make_float2(a.z, a.w),
-                     make_float2(c.x, c.y), make_float2(c.z, c.w));
-    }
-    __syncthreads();
-  }
+  permute_tiles(in, p, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
+    put_elem4<OUT>(out, o, a, b, c, e);
+  });
 }
 
 hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src_pos_of_out_bit,
@@ -446,66 +350,36 @@ hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src
   PermDesc p;
   p.rank = rank;
   for (int i = 0; i < rank; ++i) p.src_of_out[i] = src_pos_of_out_bit[i];
-  // Tile = the lo_in lowest input bits and the lo_out lowest output bits:
-  // both grown alternately while the union fits, so a permutation that keeps
-  // its low bits still gets full tiles.
+  const float2* src = reinterpret_cast<const float2*>(in);
+  PermTiles t;
+  uint32_t tgrid, n_iter;
+  if ((reinterpret_cast<uintptr_t>(in) & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 &&
+      plan_permute_tiles(rank, src_pos_of_out_bit, t, tgrid, n_iter)) {
+    if (out_store == ST_F16)
+      hipLaunchKernelGGL(k_permute_tiles<ST_F16>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
+    else if (out_store == ST_BF16)
+      hipLaunchKernelGGL(k_permute_tiles<ST_BF16>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
+    else
+      hipLaunchKernelGGL(k_permute_tiles<ST_C64>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
+    return hipGetLastError();
+  }
+  // The lo_in lowest input bits and the lo_out lowest output bits: both grown
+  // alternately while the union fits ten bits.
   int out_of_in[48];
   for (int i = 0; i < rank; ++i) out_of_in[(int)p.src_of_out[i]] = i;
-  auto tile_mask = [&](int li, int lo) {  // as output bits
+  auto tile_bits = [&](int li, int lo) {
     uint64_t m = 0;
     for (int i = 0; i < lo; ++i) m |= 1ull << i;
     for (int i = 0; i < li; ++i) m |= 1ull << out_of_in[i];
-    return m;
+    return __builtin_popcountll(m);
   };
-  int lo_in, lo_out;
-  auto grow = [&](int bits) {
-    lo_in = lo_out = 0;
-    for (bool grew = true; grew;) {
-      grew = false;
-      if (lo_out < rank && __builtin_popcountll(tile_mask(lo_in, lo_out + 1)) <= bits) ++lo_out, grew = true;
-      if (lo_in < rank && __builtin_popcountll(tile_mask(lo_in + 1, lo_out)) <= bits) ++lo_in, grew = true;
-    }
-  };
-  const float2* src = reinterpret_cast<const float2*>(in);
-  if (rank >= kPermBits && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-      (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-    // From rank 12 on a union of twelve bits always fills up (each side adds
-    // at most one bit at a time) with at least two low bits of both sides.
-    grow(kPermBits);
-    const uint64_t m = tile_mask(lo_in, lo_out);
-    PermTiles t;
-    int no = 0, nb = 0, inb[kPermBits];
-    for (int i = 0; i < rank; ++i) {
-      if ((m >> i) & 1) {
-        t.tout[nb] = (int8_t)i;
-        inb[nb++] = p.src_of_out[i];
-      } else {
-        t.oin[no] = p.src_of_out[i];
-        t.oout[no++] = (int8_t)i;
-      }
-    }
-    if (nb != kPermBits) return hipErrorInvalidValue;
-    t.n_outer = no;
-    for (int i = 0; i < kPermBits; ++i) {  // read order: by input bit
-      int rankpos = 0;
-      for (int j = 0; j < kPermBits; ++j) rankpos += inb[j] < inb[i];
-      t.tin[rankpos] = (int8_t)inb[i];
-      t.slot[rankpos] = (int8_t)i;
-    }
-    // At most 1024 workgroups (four per CU), each walking its tiles.
-    const int gbits = no < 10 ? no : 10;
-    const dim3 grid(1u << gbits);
-    const uint32_t n_iter = 1u << (no - gbits);
-    if (out_store == ST_F16)
-      hipLaunchKernelGGL(k_permute_tiles<ST_F16>, grid, dim3(256), 0, s, src, out, t, n_iter);
-    else if (out_store == ST_BF16)
-      hipLaunchKernelGGL(k_permute_tiles<ST_BF16>, grid, dim3(256), 0, s, src, out, t, n_iter);
-    else
-      hipLaunchKernelGGL(k_permute_tiles<ST_C64>, grid, dim3(256), 0, s, src, out, t, n_iter);
-    return hipGetLastError();
+  int lo_in = 0, lo_out = 0;
+  for (bool grew = true; grew;) {
+    grew = false;
+    if (lo_out < rank && tile_bits(lo_in, lo_out + 1) <= 10) ++lo_out, grew = true;
+    if (lo_in < rank && tile_bits(lo_in + 1, lo_out) <= 10) ++lo_in, grew = true;
   }
-  grow(10);
-  const uint64_t blocks = 1ull << (rank - __builtin_popcountll(tile_mask(lo_in, lo_out)));
+  const uint64_t blocks = 1ull << (rank - tile_bits(lo_in, lo_out));
   // Eight workgroups per CU, each walking many tiles (its tables are built
   // once).
   const uint64_t grid = blocks < 2048 ? blocks : 2048;
