@@ -390,7 +390,7 @@ rqc_status rqc_batch_xeb(const double* amps, uint64_t n_amps, int32_t n_qubits,
 
 /* The same with a caller-owned device workspace (8-byte aligned, at least
  * rqc_batch_xeb_workspace_bytes; its contents are overwritten): batches of
- * 2^13 amplitudes (or samples) and more are read by many workgroups, whose
+ * 2^17 amplitudes (or samples) and more are read by many workgroups, whose
  * partial sums are added in a fixed order.  0 bytes: the call runs as
  * rqc_batch_xeb. */
 rqc_status rqc_batch_xeb_workspace_bytes(uint64_t n_amps, uint64_t n_samples,

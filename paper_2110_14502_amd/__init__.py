@@ -619,13 +619,19 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     ns = 0 if samples is None else samples.numel()
     need = C.c_uint64()
     _check(_lib.rqc_batch_xeb_workspace_bytes(n, ns, C.byref(need)))
-    # The five results, then the workspace (one buffer, so one lifetime).
-    out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
-    _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits),
-                                 _ptr(samples) if samples is not None else None, ns, _ptr(out),
-                                 C.c_void_p(out.data_ptr() + 64), need.value,
-                                 _stream_handle(stream)))
-    v = out[:5].cpu().numpy()
+    sp = _ptr(samples) if samples is not None else None
+    if need.value == 0:
+        out = torch.empty(5, dtype=torch.float64, device=amps.device)
+        _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                  _stream_handle(stream)))
+        v = out.cpu().numpy()
+    else:
+        # The five results, then the workspace (one buffer, so one lifetime).
+        out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
+        _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                     C.c_void_p(out.data_ptr() + 64), need.value,
+                                     _stream_handle(stream)))
+        v = out[:5].cpu().numpy()
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 

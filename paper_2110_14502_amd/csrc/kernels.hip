@@ -405,11 +405,11 @@ namespace rqc {
 // |a|^2 over sampled entries of the batch (bounds-checked: an index outside
 // the batch makes that result NaN).
 //
-// Batches above 2^13 amplitudes are read by many workgroups (rqc_batch_xeb_ws):
-// each writes four partial sums, and one workgroup adds them in workgroup
-// order; the split depends on the batch size alone.  One workgroup reads
-// 56 GB/s (601 us for 2^21 amplitudes, 33 MB); below 2^13 the second launch
-// costs more than the reading.
+// Batches of 2^17 amplitudes and more are read by many workgroups
+// (rqc_batch_xeb_ws): each writes four partial sums, and one workgroup adds
+// them in workgroup order; the split depends on the batch size alone.  One
+// workgroup reads 56 GB/s (601 us for 2^21 amplitudes, 33 MB; 32 us split), and up to 2^16 amplitudes stay in its reach: whole calls 30 us either way at
+// 2^16, 36 against 31 us at 2^17, 24 against 29 us at 2^10.
 // ---------------------------------------------------------------------------
 constexpr int kStatThreads = 1024;
 
@@ -423,18 +423,26 @@ __device__ __forceinline__ Stats stat_range(const double* amps, uint64_t n, cons
                                             uint64_t n_samples, uint64_t first, uint64_t stride) {
   typedef double d2v __attribute__((ext_vector_type(2)));
   Stats v{0.0, 0.0, 0.0, 0};
-  // Amplitudes are read as aligned 16-byte pairs where the buffer allows it.
-  const bool pairs = (reinterpret_cast<uintptr_t>(amps) & 15) == 0;
-#pragma unroll 4
-  for (uint64_t i = first; i < n; i += stride) {
-    d2v a;
-    if (pairs) {
-      a = reinterpret_cast<const d2v*>(amps)[i];
-    } else {
-      a[0] = amps[2 * i];
-      a[1] = amps[2 * i + 1];
+  // Amplitudes are read as aligned 16-byte pairs where the buffer allows it,
+  // eight in flight per thread.
+  uint64_t i = first;
+  if ((reinterpret_cast<uintptr_t>(amps) & 15) == 0) {
+    const d2v* q = reinterpret_cast<const d2v*>(amps);
+    for (; i + 7 * stride < n; i += 8 * stride) {
+      d2v a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = q[i + u * stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double p = a[u][0] * a[u][0] + a[u][1] * a[u][1];
+        v.s1 += p;
+        v.s2 += p * p;
+      }
     }
-    const double p = a[0] * a[0] + a[1] * a[1];
+  }
+  for (; i < n; i += stride) {
+    const double re = amps[2 * i], im = amps[2 * i + 1];
+    const double p = re * re + im * im;
     v.s1 += p;
     v.s2 += p * p;
   }
@@ -520,10 +528,10 @@ __global__ __launch_bounds__(256) void k_batch_stats_sum(const double* part, int
 }
 
 // Workgroups of the split form: 2048 amplitudes (32 KB) or samples each, at
-// most four per CU; 0 below 2^13.
+// most four per CU; 0 below 2^17.
 static int stat_blocks(uint64_t n, uint64_t n_samples) {
   const uint64_t most = n > n_samples ? n : n_samples;
-  if (most < (uint64_t(1) << 13)) return 0;
+  if (most < (uint64_t(1) << 17)) return 0;
   const uint64_t b = (most + 2047) / 2048;
   return (int)(b < 1024 ? b : 1024);
 }

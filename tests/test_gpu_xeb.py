@@ -12,8 +12,8 @@ import paper_2110_14502_amd as R
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,ns,shift", [(1, 0, 0), (1000, 7, 0), (8191, 8191, 0), (8192, 1, 0), (8193, 9000, 0),
-                                        (50001, 3, 1), (5, 20000, 0), (1 << 17, 1 << 15, 0)])
+@pytest.mark.parametrize("n,ns,shift", [(1, 0, 0), (1000, 7, 0), (131071, 131071, 0), (131072, 1, 0), (131073, 9000, 0),
+                                        (190001, 3, 1), (5, 140000, 0), (1 << 18, 1 << 17, 0)])
 def test_batch_statistics_sizes(n, ns, shift):
     print("xeb", n, ns, shift, flush=True)
     g = torch.Generator(device="cuda").manual_seed(n)
