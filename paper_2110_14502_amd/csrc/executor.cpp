@@ -180,8 +180,9 @@ StepDesc make_pair_desc(const std::vector<int>& la, const std::vector<int>& lb,
     tile(d.tB, bb, pb);
     tile(d.tC, bc, pc);
   } else {
-    // tB: column bit j (in C order) -> its B position; tC: rows and the
-    // chunk's low column bits; nh_C: C positions of the chunk-selecting bits.
+    // tB: column bit j (in C order) -> its B position; tC: a wave's 64 rows and
+    // the chunk's low column bits; rw_C: C positions of the row bits that
+    // select the wave; nh_C: C positions of the chunk-selecting bits.
     d.tB.nbits = n;
     for (int j = 0; j < n; ++j) {
       d.tB.gpos[j] = (int8_t)pb(Nt[j]);
@@ -189,14 +190,16 @@ StepDesc make_pair_desc(const std::vector<int>& la, const std::vector<int>& lb,
       d.tB.cbit[j] = (int8_t)j;
     }
     std::vector<std::pair<int, int>> bcr;
-    for (int x : Rt) bcr.push_back({x, 0});
+    for (int i = 0; i < rt; ++i) {
+      if (i < 6) bcr.push_back({Rt[i], 0});
+      else d.rw_C[i - 6] = (int8_t)pc(Rt[i]);
+    }
     for (int j = 0; j < d.ncb; ++j) bcr.push_back({Nt[j], 1});
     tile(d.tC, bcr, pc);
     for (int j = d.ncb; j < n; ++j) d.nh_C[j - d.ncb] = (int8_t)pc(Nt[j]);
     // Vector stores need C's two lowest address bits to be the tile's
-    // lowest bits, and whole groups of four per thread.
-    d.vec_c = (d.tC.nbits >= 2 && d.tC.gpos[0] == 0 && d.tC.gpos[1] == 1 &&
-               d.tC.nbits >= 8) ? 1 : 0;
+    // lowest bits, and a table row of whole groups of four.
+    d.vec_c = (d.tC.nbits >= 6 && d.tC.gpos[0] == 0 && d.tC.gpos[1] == 1) ? 1 : 0;
   }
   d.rt = rt;
   d.nt = nt;

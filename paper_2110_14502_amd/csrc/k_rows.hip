@@ -19,7 +19,11 @@ namespace rqc {
 //   B_r[2k][2n] = Br  B_r[2k][2n+1] = Bi  B_r[2k+1][2n] = -Bi  B_r[2k+1][2n+1] = Br.
 // The sum is over the same indices, in another order.  Each wave handles 64
 // rows (four 16-row blocks), a workgroup 256; output columns go 8 at a time
-// through an LDS tile written out in C's own address order.
+// through an LDS tile written out in C's own address order.  The tile is the
+// wave's own (64 rows x 8 columns), so the waves of a workgroup do not wait for
+// each other within a copy (a 256-row tile took two workgroup barriers per 8
+// columns: (m, n, k) = (17, 4, 4) x 32 261 us against 242 now, (16, 7, 4) x 32
+// 728 -> 658, 16-bit (16, 7, 4) x 32 476 -> 387).
 //
 // When A is stored in FP16 / BF16 and a K chunk holds 16 or 32 complex
 // values, the products run on the 16-bit matrix cores instead
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
     gch_tab[tid] = g;
   }
   float2* Bs = rows_lds;                                    // [N][KT], columns in C's bit order
-  float* Cs = reinterpret_cast<float*>(rows_lds + N * KT);  // [R][kRowsLdc]
+  float* Cs = reinterpret_cast<float*>(rows_lds + N * KT) + wave * 64 * kRowsLdc;  // [64][kRowsLdc]
   build_tab(d.tC, kRowsLdc, 2, 0, tc);  // coordinates in floats
   for (int n = tid; n < N; n += 256) {
     int64_t o = 0;
@@ -223,7 +227,11 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
   const uint64_t rmask = n_rt - 1;
   const int rsh = d.n_ro;
   const uint64_t n_tiles = n_rt * (uint64_t)d.copies;
-  const int nC = R * NC;
+  const int nC = (R < 64 ? R : 64) * NC;  // a wave's elements per chunk of columns
+  const bool wrows = wave * 64 < R;       // whether this wave has rows
+  int64_t gwave = 0;                      // C offset of its first row in the tile
+  if (R > 64 && (wave & 1)) gwave += int64_t(1) << d.rw_C[0];
+  if (R > 128 && (wave & 2)) gwave += int64_t(1) << d.rw_C[1];
   const uint64_t per = (n_tiles + gridDim.x - 1) / gridDim.x;
   uint64_t t = (uint64_t)blockIdx.x * per;
   const uint64_t t_end = t + per < n_tiles ? t + per : n_tiles;
@@ -247,9 +255,9 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
   __syncthreads();  // tables ready
   const int64_t glo = tc.g[lane];
   const int32_t clo = tc.c[lane];
-  // Vector stores: this thread's four consecutive low elements (the same
-  // for every group it stores).
-  const int lo4 = (tid & 15) << 2;
+  // Vector stores: this lane's four consecutive low elements (the same for
+  // every group it stores).
+  const int lo4 = (lane & 15) << 2;
   const int64_t glo4 = tc.g[lo4];
   int32_t clo4[4];
 #pragma unroll
@@ -414,26 +422,26 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
       }
 #pragma unroll
       for (int h = 0; h < NCH; ++h) {
-        __syncthreads();
         // Lane holds rows 4g..4g+3 of each 16-row block at real column lc.
+        // (LDS accesses of a wave complete in order; the barriers only keep
+        // the compiler from moving them across each other.)
+        __builtin_amdgcn_wave_barrier();
         if (lc < 2 * NC) {
 #pragma unroll
           for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int r = wave * 64 + rb * 16 + 4 * g + i;
-              if (r < R) Cs[r * kRowsLdc + lc] = acc[rb][h][i];
-            }
+            for (int i = 0; i < 4; ++i) Cs[(rb * 16 + 4 * g + i) * kRowsLdc + lc] = acc[rb][h][i];
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         // The next tile's rows (loaded during this tile) are waited for here,
         // before this tile's stores are issued: the vector memory counter
         // completes in issue order, so the compiler's wait for them at the
         // hand-over below would also wait for the stores to finish.
         if (h == 0 && last_cg) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        const int64_t gch = gch_tab[cg * NCH + h];
-        // At most 2048 staged elements (256 rows x 8 columns): eight per
-        // thread, or two groups of four.  Table and staging reads are issued
+        if (!wrows) continue;
+        const int64_t gch = gch_tab[cg * NCH + h] + gwave;
+        // At most 512 staged elements (64 rows x 8 columns): eight per lane,
+        // or two groups of four.  Table and staging reads are issued
         // together before the stores so that their latencies overlap.
         if (d.vec_c) {
           int64_t g[2];
@@ -441,7 +449,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
           float2 x[2][4];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const int v = tid + 256 * u;
+            const int v = lane + 64 * u;
             const int hi = 64 + (v < (nC >> 2) ? (v >> 4) : 0);
             g[u] = tc.g[hi];
             cc[u] = tc.c[hi];
@@ -455,7 +463,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
             }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            if (tid + 256 * u >= (nC >> 2)) break;
+            if (lane + 64 * u >= (nC >> 2)) break;
             const int64_t at = oC + gch + glo4 + g[u];
             if (d.sc_store == ST_F16) store_out4<ST_F16>(d, at, x[u], sc, lmax, bad);
             else if (d.sc_store == ST_BF16) store_out4<ST_BF16>(d, at, x[u], sc, lmax, bad);
@@ -467,7 +475,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
           float2 x[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            const int e = tid + 256 * u;
+            const int e = lane + 64 * u;
             const int hi = 64 + (e < nC ? (e >> 6) : 0);
             g[u] = tc.g[hi];
             cc[u] = clo + tc.c[hi];
@@ -476,7 +484,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
           for (int u = 0; u < 8; ++u) x[u] = make_float2(Cs[cc[u]], Cs[cc[u] + 1]);
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            if (tid + 256 * u >= nC) break;
+            if (lane + 64 * u >= nC) break;
             const int64_t at = oC + gch + glo + g[u];
             if (d.sc_store == ST_F16) store_out<ST_F16>(d, at, x[u], sc, lmax, bad);
             else if (d.sc_store == ST_BF16) store_out<ST_BF16>(d, at, x[u], sc, lmax, bad);
@@ -520,7 +528,7 @@ static hipError_t launch_rows(const StepDesc& d, int sa, dim3 grid, hipStream_t 
   if (R > kRowsRows || NC > 8 || N * KT > kRowsMaxB || d.ncb > d.nt || d.kt < KB ||
       (d.kt > KB && NC != N && nch > 4) || nch > 16 || (nch > 4 && d.kt != KB))
     return hipErrorInvalidValue;
-  const size_t lds = sizeof(float2) * (size_t)N * KT + sizeof(float) * (size_t)R * kRowsLdc;
+  const size_t lds = sizeof(float2) * (size_t)N * KT + sizeof(float) * (size_t)kRowsRows * kRowsLdc;
   // Persistent grid: enough workgroups to fill every CU several times over.
   const uint64_t n_tiles = (uint64_t)d.n_row_tiles * (uint64_t)d.copies;
   grid = dim3((unsigned)std::min<uint64_t>(n_tiles, kRowsGrid), 1);
