@@ -558,31 +558,35 @@ std::vector<int8_t> perm_sources(const std::vector<int>& in, const std::vector<i
   return src;
 }
 
+// The permutation of an operand (labels `in`) into the packing order of its
+// fragments, lowest bit first: terms 0-2, rows 0-4, terms 3.., rows 5..
+std::vector<int8_t> frag_sources(const std::vector<int>& in, const std::vector<int>& rows,
+                                 const std::vector<int>& terms) {
+  std::vector<int> out;
+  auto row = [&](size_t i) { return rows[rows.size() - 1 - i]; };
+  auto term = [&](size_t i) { return terms[terms.size() - 1 - i]; };
+  for (size_t i = 0; i < 3; ++i) out.push_back(term(i));
+  for (size_t i = 0; i < 5; ++i) out.push_back(row(i));
+  for (size_t i = 3; i < terms.size(); ++i) out.push_back(term(i));
+  for (size_t i = 5; i < rows.size(); ++i) out.push_back(row(i));
+  std::reverse(out.begin(), out.end());
+  return perm_sources(in, out);
+}
+
 // An FP32 call with a long sum (shape g): per copy the operands' maxima and
 // packing (a shared operand once), the GEMM, and the FP32 kernel, which runs
 // only if an operand was flagged.
 void pair_split32(const Split32Shape& g, const std::vector<int>& la, const std::vector<int>& lb,
                   const std::vector<int>& lc, const void* A, const void* B, void* C, int32_t batch,
                   int64_t stride_a, int64_t stride_b, int64_t stride_c, char* ws, hipStream_t s) {
-  // Fragment order, lowest bit first: terms 0-2, rows 0-4, terms 3.., rows 5..
-  auto sources = [&](const std::vector<int>& in, const std::vector<int>& free_labels) {
-    const int nf = (int)free_labels.size();
-    std::vector<int> out;  // lowest bit first
-    auto row = [&](int i) { return free_labels[nf - 1 - i]; };
-    auto term = [&](int i) { return g.K[g.k - 1 - i]; };
-    for (int i = 0; i < 3; ++i) out.push_back(term(i));
-    for (int i = 0; i < 5; ++i) out.push_back(row(i));
-    for (int i = 3; i < g.k; ++i) out.push_back(term(i));
-    for (int i = 5; i < nf; ++i) out.push_back(row(i));
-    std::reverse(out.begin(), out.end());
-    return perm_sources(in, out);
-  };
   const std::vector<int>&lr = g.swap ? lb : la, &lcl = g.swap ? la : lb;  // row and column operand
-  const std::vector<int8_t> src_r = sources(lr, g.Mf), src_c = sources(lcl, g.Nf);
+  const std::vector<int8_t> src_r = frag_sources(lr, g.Mf, g.K),
+                            src_c = frag_sources(lcl, g.Nf, g.K);
   rqc::SplitHdr* hdr = reinterpret_cast<rqc::SplitHdr*>(ws);
   uint32_t* part_r = reinterpret_cast<uint32_t*>(ws + 256);
   uint32_t* part_c = part_r + rqc::kSplitParts;
-  rqc::SplitDesc d{};
+  rqc::FragDesc d{};
+  d.copies = 1;
   d.A = ws + g.hdr;
   d.B = d.A + g.bytes_a;
   d.hdr = hdr;
@@ -733,25 +737,22 @@ rqc_status rqc_pair_contract_ws(const int32_t* labels_a, int32_t rank_a, const i
   const int lp = prec == RQC_F16 ? rqc::ST_F16 : rqc::ST_BF16;
   uint8_t* wa = static_cast<uint8_t*>(workspace);
   uint8_t* wb = wa + g.bytes_a;
-  std::vector<int> oa(g.Mf), ob(g.Nf);
-  oa.insert(oa.end(), g.K.begin(), g.K.end());
-  ob.insert(ob.end(), g.K.begin(), g.K.end());
-  const std::vector<int8_t> srca = perm_sources(la, oa), srcb = perm_sources(lb, ob);
+  const std::vector<int8_t> srca = frag_sources(la, g.Mf, g.K), srcb = frag_sources(lb, g.Nf, g.K);
   const uint64_t ea = uint64_t(1) << (g.m + g.k), eb = uint64_t(1) << (g.n + g.k);
   for (uint64_t j = 0; j < g.copies_a; ++j)
-    rqc::hip_check(rqc::launch_permute(static_cast<const float2*>(A) + j * stride_a, wa + j * ea * 4,
-                                       rank_a, srca.data(), s, lp),
+    rqc::hip_check(rqc::launch_pack16(static_cast<const float2*>(A) + j * stride_a,
+                                      reinterpret_cast<char*>(wa + j * ea * 4), rank_a, srca.data(), lp, s),
                    "pack A");
   for (uint64_t j = 0; j < g.copies_b; ++j)
-    rqc::hip_check(rqc::launch_permute(static_cast<const float2*>(B) + j * stride_b, wb + j * eb * 4,
-                                       rank_b, srcb.data(), s, lp),
+    rqc::hip_check(rqc::launch_pack16(static_cast<const float2*>(B) + j * stride_b,
+                                      reinterpret_cast<char*>(wb + j * eb * 4), rank_b, srcb.data(), lp, s),
                    "pack B");
-  rqc::Gemm16Desc d{};
-  d.A = reinterpret_cast<const uint32_t*>(wa);
-  d.B = reinterpret_cast<const uint32_t*>(wb);
+  rqc::FragDesc d{};
+  d.A = reinterpret_cast<const char*>(wa);
+  d.B = reinterpret_cast<const char*>(wb);
   d.C = C;
-  d.sA = g.copies_a > 1 ? (int64_t)ea : 0;
-  d.sB = g.copies_b > 1 ? (int64_t)eb : 0;
+  d.sA = g.copies_a > 1 ? (int64_t)ea * 4 : 0;
+  d.sB = g.copies_b > 1 ? (int64_t)eb * 4 : 0;
   d.sC = stride_c;
   d.m = g.m;
   d.n = g.n;

@@ -213,57 +213,45 @@ hipError_t launch_batch_stats(const double* amps, uint64_t n, int n_qubits, cons
 uint64_t batch_stats_workspace(uint64_t n, uint64_t n_samples);
 hipError_t launch_add_f64(double* dst, const double* src, int64_t n, hipStream_t s);
 // Bit permutation out (bit i fed by input bit src_pos_of_out_bit[i]) of a
-// complex64 tensor; out_store ST_F16 / ST_BF16 writes packed 16-bit (re, im)
-// words (round to nearest, no scaling).
+// complex64 tensor.
 hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src_pos_of_out_bit,
-                          hipStream_t s, int out_store = ST_C64);
+                          hipStream_t s);
 
-// 16-bit matrix-core GEMM of the two-phase long-sum contraction
-// (k_gemm16.hip): A [copy][2^m rows][2^k] and B [copy][2^n columns][2^k]
-// packed 16-bit (re, im) words, summed index lowest and in the same order in
-// both; C (complex64) element (row r, column c) of copy j at
+// GEMM of the two-phase long-sum contractions on packed fragments
+// (frag_gemm.h; k_gemm16.hip: FP16 / BF16 complex values; k_split32.hip: FP32
+// values as two FP16 halves, three planes of plane_a / plane_b bytes).  C
+// (complex64) element (row r, column c) of copy j at
 // j * sC + sum_b bit_b(r) 2^crow[b] + sum_b bit_b(c) 2^ccol[b].
-constexpr int kGemm16M = 256, kGemm16N = 128, kGemm16K = 32;  // tile rows, complex columns, chunk k
-struct Gemm16Desc {
-  const uint32_t* A;
-  const uint32_t* B;
-  void* C;
-  int64_t sA, sB, sC;  // copy strides: words of A and B (0 = shared), complex elements of C
-  int32_t m, n, k;     // bits: rows (>= 8), columns (>= 7), summed (>= 5)
-  int32_t copies;
-  int32_t ksplit;      // the sum split 2^ksplit ways (partials in P, then reduced)
-  float2* P;           // partials [copy][split][row][column], when ksplit > 0
-  int8_t crow[40];
-  int8_t ccol[40];
-};
-hipError_t launch_gemm16(const Gemm16Desc& d, int lp_kind, hipStream_t s);
-// C = the partials of a split sum added in split order (also used by the FP32
-// split-halves GEMM).
-hipError_t launch_gemm16_reduce(const Gemm16Desc& d, hipStream_t s);
-
-// FP32 long sums on the FP16 matrix cores (k_split32.hip).  A and B packed as
-// fragments of FP16 halves, three planes of plane_a / plane_b bytes (12 bytes
-// per element in all); element (row, column) of C as in Gemm16Desc.
-constexpr int kSplitM = 256, kSplitN = 128;  // output tile
-constexpr int kSplitParts = 1024;            // partial maxima per operand
-struct SplitDesc {
+constexpr int kGemm16M = 256, kGemm16N = 128;  // output tile: rows, complex columns
+struct FragDesc {
   const char* A;
   const char* B;
   void* C;
-  const SplitHdr* hdr;
+  const SplitHdr* hdr;     // split halves only
+  int64_t sA, sB, sC;      // copy strides: bytes of A and B (0 = shared), complex elements of C
   int64_t plane_a, plane_b;
-  int32_t m, n, k;     // bits: rows (>= 8), columns (>= 7), summed (6..24)
-  int32_t ksplit;      // the sum split 2^ksplit ways (partials in P, then reduced)
-  float2* P;           // partials [split][row][column]
+  int32_t m, n, k;         // bits: rows (>= 8), columns (>= 7), summed (>= 7)
+  int32_t copies;
+  int32_t ksplit;          // the sum split 2^ksplit ways (partials in P, then reduced)
+  float2* P;               // partials [copy][split][row][column], when ksplit > 0
   int8_t crow[40];
   int8_t ccol[40];
 };
-// Largest components, then packing, of one operand: rank bits, src_of_out the
-// permutation into fragment order, `right` for B.
+// Packing of one operand into fragments: rank bits, src_of_out the permutation
+// into the packing order (frag_at).
+hipError_t launch_pack16(const void* in, char* out, int rank, const int8_t* src_of_out, int lp_kind,
+                         hipStream_t s);
+hipError_t launch_gemm16(const FragDesc& d, int lp_kind, hipStream_t s);
+// C = the partials of a split sum added in split order.
+hipError_t launch_gemm16_reduce(const FragDesc& d, hipStream_t s);
+
+// FP32 long sums on the FP16 matrix cores: largest components, then packing, of
+// one operand (`right` for B), 12 bytes per element in all.
+constexpr int kSplitParts = 1024;  // partial maxima per operand
 hipError_t launch_split_pack(const void* in, char* out, int rank, const int8_t* src_of_out,
                              int64_t plane, bool right, uint32_t* part, int32_t* flag,
                              int32_t* scale_exp, hipStream_t s);
-hipError_t launch_split_gemm(const SplitDesc& d, hipStream_t s);
+hipError_t launch_split_gemm(const FragDesc& d, hipStream_t s);
 hipError_t launch_cgemm(int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
                         hipStream_t s);
 

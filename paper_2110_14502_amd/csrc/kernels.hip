@@ -179,8 +179,8 @@ hipError_t launch_add_f64(double* dst, const double* src, int64_t n, hipStream_t
 }
 
 // ---------------------------------------------------------------------------
-// Bit permutation (the separate-permutation baseline, and the packing phase
-// of the two-phase contractions, which also converts): tiles staged through
+// Bit permutation (the separate-permutation baseline; the packing kernels of
+// the two-phase contractions share the tile walk): tiles staged through
 // LDS so that both the reads (low input bits) and the writes (low output
 // bits) are contiguous.  Bound by HBM.
 //
@@ -199,60 +199,7 @@ struct PermDesc {
   int8_t src_of_out[48];  // input bit feeding output bit i
 };
 
-template <int OUT>
-__device__ __forceinline__ void put_elem(void* out, uint64_t i, float2 v);
-template <>
-__device__ __forceinline__ void put_elem<ST_C64>(void* out, uint64_t i, float2 v) {
-  reinterpret_cast<float2*>(out)[i] = v;
-}
-template <>
-__device__ __forceinline__ void put_elem<ST_F16>(void* out, uint64_t i, float2 v) {
-  h2 o;
-  o.x = (_Float16)v.x;
-  o.y = (_Float16)v.y;
-  reinterpret_cast<h2*>(out)[i] = o;
-}
-template <>
-__device__ __forceinline__ void put_elem<ST_BF16>(void* out, uint64_t i, float2 v) {
-  b2 o;
-  o.x = (__bf16)v.x;
-  o.y = (__bf16)v.y;
-  reinterpret_cast<b2*>(out)[i] = o;
-}
-
-// Four consecutive output elements from one aligned group (the output's two
-// lowest bits are the tile's): one 16-byte store of packed 16-bit words, or
-// two of complex64.
-template <int OUT>
-__device__ __forceinline__ void put_elem4(void* out, uint64_t i, float2 a, float2 b, float2 c,
-                                          float2 e) {
-  if constexpr (OUT == ST_C64) {
-    float4* o = reinterpret_cast<float4*>(reinterpret_cast<float2*>(out) + i);
-    o[0] = make_float4(a.x, a.y, b.x, b.y);
-    o[1] = make_float4(c.x, c.y, e.x, e.y);
-  } else {
-    uint32_t w[4];
-    const float2 v[4] = {a, b, c, e};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (OUT == ST_F16) {
-        h2 x;
-        x.x = (_Float16)v[j].x;
-        x.y = (_Float16)v[j].y;
-        w[j] = __builtin_bit_cast(uint32_t, x);
-      } else {
-        b2 x;
-        x.x = (__bf16)v[j].x;
-        x.y = (__bf16)v[j].y;
-        w[j] = __builtin_bit_cast(uint32_t, x);
-      }
-    }
-    *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(out) + i) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-}
-
-template <int OUT>
-__global__ __launch_bounds__(256) void k_permute(const float2* in, void* out, PermDesc p,
+__global__ __launch_bounds__(256) void k_permute(const float2* in, float2* out, PermDesc p,
                                                  int lo_in, int lo_out, uint64_t n_blocks) {
   // Tile = the lowest `lo_in` input bits  U  the lowest `lo_out` output bits.
   // The tile's element offsets (relative to the tile base) and LDS slots are
@@ -332,35 +279,33 @@ __global__ __launch_bounds__(256) void k_permute(const float2* in, void* out, Pe
     }
     __syncthreads();
     for (int t = threadIdx.x; t < nte; t += blockDim.x)
-      put_elem<OUT>(out, base_out + toff_out[t], tile[t + (t >> 5)]);
+      out[base_out + toff_out[t]] = tile[t + (t >> 5)];
     __syncthreads();
   }
 }
 
-template <int OUT>
-__global__ __launch_bounds__(256) void k_permute_tiles(const float2* in, void* out, PermTiles p,
+__global__ __launch_bounds__(256) void k_permute_tiles(const float2* in, float2* out, PermTiles p,
                                                        uint32_t n_iter) {
   permute_tiles(in, p, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
-    put_elem4<OUT>(out, o, a, b, c, e);
+    float4* q = reinterpret_cast<float4*>(out + o);
+    q[0] = make_float4(a.x, a.y, b.x, b.y);
+    q[1] = make_float4(c.x, c.y, e.x, e.y);
   });
 }
 
 hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src_pos_of_out_bit,
-                          hipStream_t s, int out_store) {
+                          hipStream_t s) {
   PermDesc p;
   p.rank = rank;
   for (int i = 0; i < rank; ++i) p.src_of_out[i] = src_pos_of_out_bit[i];
   const float2* src = reinterpret_cast<const float2*>(in);
+  float2* dst = reinterpret_cast<float2*>(out);
   PermTiles t;
   uint32_t tgrid, n_iter;
   if ((reinterpret_cast<uintptr_t>(in) & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 &&
       plan_permute_tiles(rank, src_pos_of_out_bit, t, tgrid, n_iter)) {
-    if (out_store == ST_F16)
-      hipLaunchKernelGGL(k_permute_tiles<ST_F16>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
-    else if (out_store == ST_BF16)
-      hipLaunchKernelGGL(k_permute_tiles<ST_BF16>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
-    else
-      hipLaunchKernelGGL(k_permute_tiles<ST_C64>, dim3(tgrid), dim3(256), 0, s, src, out, t, n_iter);
+    t.aligned = 1;
+    hipLaunchKernelGGL(k_permute_tiles, dim3(tgrid), dim3(256), 0, s, src, dst, t, n_iter);
     return hipGetLastError();
   }
   // The lo_in lowest input bits and the lo_out lowest output bits: both grown
@@ -383,15 +328,8 @@ hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src
   // Eight workgroups per CU, each walking many tiles (its tables are built
   // once).
   const uint64_t grid = blocks < 2048 ? blocks : 2048;
-  if (out_store == ST_F16)
-    hipLaunchKernelGGL(k_permute<ST_F16>, dim3((unsigned)grid), dim3(256), 0, s, src, out, p, lo_in,
-                       lo_out, blocks);
-  else if (out_store == ST_BF16)
-    hipLaunchKernelGGL(k_permute<ST_BF16>, dim3((unsigned)grid), dim3(256), 0, s, src, out, p,
-                       lo_in, lo_out, blocks);
-  else
-    hipLaunchKernelGGL(k_permute<ST_C64>, dim3((unsigned)grid), dim3(256), 0, s, src, out, p,
-                       lo_in, lo_out, blocks);
+  hipLaunchKernelGGL(k_permute, dim3((unsigned)grid), dim3(256), 0, s, src, dst, p, lo_in, lo_out,
+                     blocks);
   return hipGetLastError();
 }
 

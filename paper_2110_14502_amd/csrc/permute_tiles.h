@@ -11,6 +11,7 @@ constexpr int kPermBits = 12;                              // tile bits
 constexpr int kPermGroups = (1 << kPermBits) / (4 * 256);  // groups of four elements per thread
 struct PermTiles {
   int32_t n_outer;
+  int32_t aligned;          // the input is 16-byte aligned
   int8_t tin[kPermBits];    // input address bit of read-order bit i (ascending)
   int8_t slot[kPermBits];   // output-order bit of read-order bit i
   int8_t tout[kPermBits];   // output address bit of output-order bit i (ascending)
@@ -77,9 +78,16 @@ __device__ __forceinline__ void permute_tiles(const float2* in, const PermTiles&
   auto load = [&]() {
 #pragma unroll
     for (int g = 0; g < kPermGroups; ++g) {
-      const float4* src = reinterpret_cast<const float4*>(in + base_in + off_in + gin[g]);
-      v[g][0] = src[0];
-      v[g][1] = src[1];
+      const float2* q = in + base_in + off_in + gin[g];
+      if (p.aligned) {
+        const float4* src = reinterpret_cast<const float4*>(q);
+        v[g][0] = src[0];
+        v[g][1] = src[1];
+      } else {
+        const float2 a = q[0], b = q[1], c = q[2], e = q[3];
+        v[g][0] = make_float4(a.x, a.y, b.x, b.y);
+        v[g][1] = make_float4(c.x, c.y, e.x, e.y);
+      }
     }
   };
   load();
