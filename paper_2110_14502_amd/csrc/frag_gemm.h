@@ -49,18 +49,6 @@ constexpr int kFragBBuf = kGemm16N / 32 * kFragBlk;     // 16 KB
 
 constexpr int kFragBuf = kFragABuf + kFragBBuf;
 
-// 16 bytes per lane from memory to LDS: lane i's go to LDS byte dst + 16 i (dst
-// uniform).  In assembly because the compiler waits for every copy in flight
-// before any LDS read when it places the waits itself; the kernel's own wait
-// before the barrier covers them.  No vector register is written; M0, the LDS
-// address, has no other use in this kernel and must be set one wait state ahead.
-__device__ __forceinline__ void frag_copy(const char* src, uint32_t dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
-                   __builtin_amdgcn_readfirstlane(dst)),
-               "v"(src)
-               : "memory");
-}
-
 template <int LP>
 __device__ __forceinline__ floatx16 frag_mfma(frag_u4 a, frag_u4 b, floatx16 c) {
   if constexpr (LP == ST_F16)
@@ -126,16 +114,16 @@ __global__ __launch_bounds__(512, 1) void k_frag_gemm(FragDesc d) {
   const int64_t piece = (int64_t)(wv >> 1) * blk + (int64_t)(ks << lg) * kFragBlk + (wv & 1) * kFragBytes;
   const char* At = d.A + copy * d.sA + (int64_t)(rt * (kGemm16M / 32)) * blk + piece + lane * 16;
   const char* Bt = d.B + copy * d.sB + (int64_t)(ct * (kGemm16N / 32)) * blk + piece + lane * 16;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds +
+  const uint32_t lds0 = lds_address(lds) +
                         (uint32_t)((wv >> 1) * kFragBlk + (wv & 1) * kFragBytes);
   // Copy j of half `sub` of chunk q: blocks 0-3 and 4-7 of A, then B.
   auto copy1 = [&](int q, int sub, int buf, int j) {
     const int64_t at = (int64_t)(q & (n_kc - 1)) * kFragBlk + sub * 2 * kFragBytes;
     const uint32_t l = lds0 + (uint32_t)(buf * kFragBuf + sub * 2 * kFragBytes);
     if (j < 2)
-      frag_copy(At + (MODE == 0 ? (q >> lg) * d.plane_a : 0) + at + j * 4 * blk, l + j * 4 * kFragBlk);
+      lds_copy16(At + (MODE == 0 ? (q >> lg) * d.plane_a : 0) + at + j * 4 * blk, l + j * 4 * kFragBlk);
     else
-      frag_copy(Bt + (MODE == 0 ? (q >> lg) * d.plane_b : 0) + at, l + kFragABuf);
+      lds_copy16(Bt + (MODE == 0 ? (q >> lg) * d.plane_b : 0) + at, l + kFragABuf);
   };
   auto fetch = [&](int q, int sub, int buf) {
     for (int j = 0; j < 3; ++j) copy1(q, sub, buf, j);

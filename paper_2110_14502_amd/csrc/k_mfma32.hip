@@ -345,6 +345,352 @@ __global__ __launch_bounds__(256, 2) void k_mfma32(StepDesc d, uint64_t n_items)
 }
 
 // ---------------------------------------------------------------------------
+// The persistent walk for complex64 operands in the planner's layout (the
+// summed indices lowest in A and B): chunks are copied straight into LDS, 16
+// bytes (two summed terms of a row) per lane, instead of passing through
+// registers.  The arithmetic is k_mfma32's three-product form in the same
+// order: the same bits.
+//
+// What bounds it: the FP32 matrix products (64 cycles each) and, for short sums,
+// memory at the same time.  The FP32 products run on the vector ALUs: every
+// other vector instruction costs about 6 cycles of product time, and 17 where the
+// next product waits for its result.  So a step of six products has three
+// further vector instructions, the sums for the three-product form, made a step
+// ahead; LDS addresses are constants beside two bases per operand, copies take
+// a scalar base, a tile's first products a zero sum, and outer indices are
+// worked out in scalar registers.
+//
+// LDS holds blocks of 8 rows, each [4][8 rows][2 pairs of terms]: the copying
+// lanes choose what lands where by their source address (two lanes read 32
+// consecutive bytes), and odd blocks swap the two pairs, so that the rows a wave
+// reads at one step meet two to a bank.  Three buffers: the copies of the chunk
+// after next go out one a step; a chunk's last step waits for the next chunk,
+// meets the one barrier and reads its first operands, among its products.
+//
+// Output: each wave stages its 64 x 32 block itself, 16 rows at a time, in the
+// buffer of the last chunk, two elements per lane and store.  74 KB of LDS, two
+// workgroups per CU.
+//
+// Measured against k_mfma32 (and the per-tile kernel where that was the choice):
+// 2^(14+6) x 2^(7+6), 37 copies 390 -> 308 us; 2^(16+7) x 2^(7+7), 32 copies
+// 2232 -> 1936; 2^(9+10) x 2^(8+10), 32 copies 234 -> 206 (125 TFLOP/s
+// executed of 157); 2^(8+13) x 2^(7+13), 32 copies 1232 -> 901.
+// ---------------------------------------------------------------------------
+constexpr int kDmaA = kTM * 128, kDmaB = kTN * 128;  // bytes of a chunk (16 terms of 8 bytes per row)
+constexpr int kDmaBuf = kDmaA + kDmaB;
+constexpr int kDmaLdc = 33;                          // complex values per staged row
+static_assert(4 * 16 * kDmaLdc * 8 <= kDmaBuf, "the staged rows of four waves fit one buffer");
+
+template <int SC>
+__global__ __launch_bounds__(256, 2) void k_mfma32_copy(StepDesc d, uint32_t n_items) {
+  __shared__ __attribute__((aligned(16))) char lds[3 * kDmaBuf];
+  __shared__ int64_t cg[72];  // C offset of a staged element: low six bits, then the rest
+  __shared__ int32_t cc[72];  // its place in the staging area
+  __shared__ float red[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l = lane & 31, h = lane >> 5;
+  const OuterReg ot = outer_reg(d);
+
+  // Byte offsets of the copies: block i = 4 wave + j of A's rows, 2 wave + j of
+  // B's columns.
+  uint32_t gA[4], gB[2];
+  {
+    const int p = (lane >> 4) * 2 + (lane & 1), r = (lane >> 1) & 7;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = (4 * wave + j) * 8 + r;
+      gA[j] = 16 * (p ^ (j & 1));
+      for (int b = 4; b < d.tA.nbits; ++b)
+        if ((row >> d.tA.cbit[b]) & 1) gA[j] += 8u << d.tA.gpos[b];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = (2 * wave + j) * 8 + r;
+      gB[j] = 16 * (p ^ (j & 1));
+      for (int b = 4; b < d.tB.nbits; ++b)
+        if ((col >> d.tB.cbit[b]) & 1) gB[j] += 8u << d.tB.gpos[b];
+    }
+  }
+  // Staged elements: row bits 0-3 and column bits 0-4 in C's address order;
+  // the other tile bits select the pass and the wave.
+  int64_t rw[3] = {0, 0, 0}, cw = 0;  // C weights of row bits 4, 5, 6 and column bit 5
+  bool vec_c = false;                 // C's address bit 0 is staged bit 0: stores of two elements
+  {
+    int64_t g = 0;
+    int c = 0, n = 0;
+    const int v = tid < 64 ? tid : tid - 64, b0 = tid < 64 ? 0 : 6, b1 = tid < 64 ? 6 : 9;
+    for (int b = 0; b < d.tC.nbits; ++b) {
+      const int role = d.tC.role[b], cb = d.tC.cbit[b], gp = d.tC.gpos[b];
+      if (role == 0 && cb >= 4) {
+        if (cb == 4) rw[0] = int64_t(1) << gp;
+        if (cb == 5) rw[1] = int64_t(1) << gp;
+        if (cb == 6) rw[2] = int64_t(1) << gp;
+        continue;
+      }
+      if (role == 1 && cb == 5) {
+        cw = int64_t(1) << gp;
+        continue;
+      }
+      if (gp == 0) vec_c = true;
+      if (n >= b0 && n < b1 && ((v >> (n - b0)) & 1)) {
+        g += int64_t(1) << gp;
+        c += role == 0 ? kDmaLdc << cb : 1 << cb;
+      }
+      ++n;
+    }
+    if (tid < 72) {
+      cg[tid] = g;
+      cc[tid] = c;
+    }
+  }
+  __syncthreads();
+  const int64_t g_wave = (wm ? rw[2] : 0) + (wn ? cw : 0);
+  const int lo = vec_c ? (lane & 31) << 1 : lane;
+  const int64_t g_lo = cg[lo];
+  const int c_lo = cc[lo], c_lo1 = vec_c ? cc[lo + 1] : 0;
+
+  // Items as in k_mfma32: step i of the walk covers items i G .. i G + G - 1,
+  // consecutive ones on one XCD.
+  const int n_ko = __builtin_amdgcn_readfirstlane(d.n_ko), n_kc = 1 << n_ko;
+  const int tb = d.n_ro + d.n_no;
+  const uint32_t tmask = (1u << tb) - 1, cmask = (1u << d.n_no) - 1;
+  const uint32_t G = gridDim.x;
+  uint32_t t = (G & 7) == 0 ? (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  auto item_offsets = [&](uint32_t it, int64_t& oA, int64_t& oB, int64_t& oC) {
+    const int copy = (int)(it >> tb);
+    const uint32_t bid = it & tmask;
+    const int js = copy % d.gs_c, jb = copy / d.gs_c;
+    int64_t cr = 0, cn = 0;
+    oA = js * d.sA_s + jb * d.sA_b;
+    oB = js * d.sB_s + jb * d.sB_b;
+    outer_sum(ot.rn, bid >> d.n_no, oA, cr);
+    outer_sum(ot.rn >> 16, bid & cmask, oB, cn);
+    oC = js * d.sC_s + jb * d.sC_b + cr + cn;
+  };
+
+  // The next chunk to copy: chunk fk of item ft (whose operands start at iA,
+  // iB), at fA, fB.
+  uint32_t ft = t;
+  int fk = -1;
+  int64_t iA = 0, iB = 0;
+  const float2 *fA = nullptr, *fB = nullptr;
+  const uint32_t l0 = lds_address(lds);
+  auto fetch1 = [&](int j, uint32_t at) {  // at: LDS address of the buffer
+    if (j < 4) lds_copy16(fA, gA[j], at + (uint32_t)((4 * wave + j) * 1024));
+    else lds_copy16(fB, gB[j - 4], at + (uint32_t)(kDmaA + (2 * wave + j - 4) * 1024));
+  };
+  auto advance = [&]() {
+    if (ft >= n_items) return;
+    if (++fk == n_kc) {
+      fk = 0;
+      ft += G;
+      if (ft >= n_items) return;
+      int64_t oC;
+      item_offsets(ft, iA, iB, oC);
+    }
+    int64_t kA = iA, kB = iB;
+    outer_sum(ot.k, (uint32_t)fk, kA, kB);
+    fA = static_cast<const float2*>(d.A) + kA;
+    fB = static_cast<const float2*>(d.B) + kB;
+  };
+  auto fetch = [&](int buf) {
+    if (ft < n_items)
+#pragma unroll
+      for (int j = 0; j < 6; ++j) fetch1(j, l0 + (uint32_t)(buf * kDmaBuf));
+    advance();
+  };
+
+  // Lane half h takes summed term 2 kk + h of row (column) l at step kk.
+  const int at_l = (l >> 3) * 1024 + (l & 7) * 32 + h * 8, sw = ((l >> 3) & 1) * 16;
+  const int a_at = wm * 8192 + at_l, b_at = kDmaA + wn * 4096 + at_l;
+  float2 a0, a1, b;    // the operands of the step at hand
+  float as0, as1, bs;  // and their sums
+  int aE, aO, bE, bO;  // LDS offsets of a chunk's even and odd steps
+  auto at_buf = [&](int buf) {
+    aE = buf * kDmaBuf + a_at + sw;
+    aO = buf * kDmaBuf + a_at + 16 - sw;
+    bE = buf * kDmaBuf + b_at + sw;
+    bO = buf * kDmaBuf + b_at + 16 - sw;
+  };
+  auto rd = [&](int at) { return *reinterpret_cast<const float2*>(lds + at); };
+
+  Scale sc{0, 0}, nsc{0, 0};
+  bool stored = false;  // output was stored since chunk c + 1's copies were issued
+  if (t < n_items) {
+    const int copy = (int)(t >> tb);
+    nsc = compute_scale_s(d, copy % d.gs_c, copy / d.gs_c);
+    int64_t oC;
+    item_offsets(t, iA, iB, oC);
+    advance();
+    fetch(0);
+    fetch(1);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    plain_barrier();
+    at_buf(0);
+    a0 = rd(aE);
+    a1 = rd(aE + 4096);
+    b = rd(bE);
+    as0 = a0.x + a0.y;
+    as1 = a1.x + a1.y;
+    bs = b.x + b.y;
+  }
+  int buf = 0, cur = -1, cjs = 0, cjb = 0, bad = 0;
+  bool wexp = false;
+  float lmax = 0.f;
+  for (; t < n_items; t += G) {
+    const int copy = (int)(t >> tb);
+    const uint32_t bid = t & tmask;
+    const int js = copy % d.gs_c, jb = copy / d.gs_c;
+    if (copy != cur) {
+      if (cur >= 0) finish_scale<256>(d, cjs, cjb, lmax, bad, red, wexp, sc);
+      sc = nsc;
+      lmax = 0.f;
+      bad = 0;
+      wexp = false;
+      cur = copy;
+      cjs = js;
+      cjb = jb;
+    }
+    wexp = wexp || bid == 0;
+    if (t + G < n_items) {
+      const int cn = (int)((t + G) >> tb);
+      if (cn != copy) nsc = compute_scale_s(d, cn % d.gs_c, cn / d.gs_c);
+    }
+    Acc32<true> acc;
+    auto mma = [&](int i, float x, float y, bool zero) {
+      if (zero) {  // a tile's first products take a zero sum
+        floatx16 z;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r] = 0.f;
+        acc.v[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, z, 0, 0, 0);
+      } else {
+        acc.v[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc.v[i], 0, 0, 0);
+      }
+    };
+    for (int kc = 0; kc < n_kc; ++kc) {
+      const int nb = buf == 2 ? 0 : buf + 1;
+      const uint32_t fat = __builtin_amdgcn_readfirstlane(l0 + (uint32_t)((buf == 0 ? 2 : buf - 1) * kDmaBuf));
+      // ft < n_items (below 2^31), as a scalar: chunk c + 2's copies go out one a step.
+      const uint32_t more = (ft - n_items) >> 31;
+      __builtin_amdgcn_s_setprio(1);
+      auto step = [&](int kk, bool zero) {
+        float2 na0, na1, nb0;
+        if (kk + 1 < kTK / 2) {
+          const int o = ((kk + 1) >> 1) * 256;
+          na0 = rd((kk & 1 ? aE : aO) + o);
+          na1 = rd((kk & 1 ? aE : aO) + o + 4096);
+          nb0 = rd((kk & 1 ? bE : bO) + o);
+        }
+        // The scheduling barriers keep the reads ahead of four products and the
+        // sums for the next step among this step's.
+        __builtin_amdgcn_sched_barrier(0);
+        mma(0, a0.x, b.x, zero);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kk < 6 && more) fetch1(kk, fat);
+        if (kk == 6) advance();
+        if (kk + 1 == kTK / 2) {
+          // Every read of this chunk is done and chunk c + 1 has landed: its
+          // copies are older than chunk c + 2's six and, after a tile's end,
+          // than that tile's stores (16 at the least; the count completes in
+          // order, so a wait past them would wait for them too).
+          asm volatile("" ::: "memory");
+          if (!more) __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0)
+          else if (stored) __builtin_amdgcn_s_waitcnt(0x4076);    // vmcnt(22) lgkmcnt(0)
+          else __builtin_amdgcn_s_waitcnt(0x0076);                // vmcnt(6) lgkmcnt(0)
+          plain_barrier();
+          at_buf(nb);
+          na0 = rd(aE);
+          na1 = rd(aE + 4096);
+          nb0 = rd(bE);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        mma(1, a0.y, b.y, zero);
+        mma(2, as0, bs, zero);
+        mma(3, a1.x, b.x, zero);
+        mma(4, a1.y, b.y, zero);
+        __builtin_amdgcn_sched_barrier(0);
+        float nas0 = na0.x + na0.y, nas1 = na1.x + na1.y, nbs = nb0.x + nb0.y;
+        asm volatile("" : "+v"(nas0), "+v"(nas1), "+v"(nbs));
+        __builtin_amdgcn_sched_barrier(0);
+        mma(5, as1, bs, zero);
+        a0 = na0;
+        a1 = na1;
+        b = nb0;
+        as0 = nas0;
+        as1 = nas1;
+        bs = nbs;
+      };
+      if (kc == 0) step(0, true);
+      else step(0, false);
+#pragma unroll
+      for (int kk = 1; kk < kTK / 2; ++kk) step(kk, false);
+      __builtin_amdgcn_s_setprio(0);
+      stored = false;
+      if (kc + 1 < n_kc) buf = nb;
+    }
+    // The last chunk's buffer is free (the barrier in its last step).
+    int64_t oA, oB, oC;
+    item_offsets(t, oA, oB, oC);
+    float2* Cs = reinterpret_cast<float2*>(lds + buf * kDmaBuf) + wave * 16 * kDmaLdc;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        // Rows 32 i + 16 hf .. + 15: lane (h, l) holds rows 8 (r / 4) + 4 h + r
+        // mod 4 of column l.
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const float p1 = acc.v[3 * i][8 * hf + r], p2 = acc.v[3 * i + 1][8 * hf + r];
+          const float p3 = acc.v[3 * i + 2][8 * hf + r];
+          Cs[(8 * (r >> 2) + 4 * h + (r & 3)) * kDmaLdc + l] = make_float2(p1 - p2, p3 - p1 - p2);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t at = oC + g_wave + (i ? rw[1] : 0) + (hf ? rw[0] : 0) + g_lo;
+        if (vec_c) {
+          float2 x[4][2];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int c = cc[64 + 2 * u + (lane >> 5)];
+            x[u][0] = Cs[c_lo + c];
+            x[u][1] = Cs[c_lo1 + c];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            store_out2<SC>(d, at + cg[64 + 2 * u + (lane >> 5)], x[u], sc, lmax, bad);
+        } else {
+          float2 x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) x[u] = Cs[c_lo + cc[64 + u]];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) store_out<SC>(d, at + cg[64 + u], x[u], sc, lmax, bad);
+        }
+      }
+    // Every wave is done with the buffer before copies go into it.
+    plain_barrier();
+    stored = true;
+    buf = buf == 2 ? 0 : buf + 1;
+  }
+  if (cur >= 0) finish_scale<256>(d, cjs, cjb, lmax, bad, red, wexp, sc);
+}
+
+// Whether a step's tiles can be copied in 16-byte pairs: the chunk's summed
+// bits are A's and B's address bits 0-3, in order, a tile's offsets fit 32 bits,
+// and the operands (with every copy stride) keep 16-byte alignment.
+static bool copy_fits(const StepDesc& d, int sa, int sb, uint64_t n_items) {
+  if (sa != ST_C64 || sb != ST_C64 || d.run_if || n_items >= (uint64_t(1) << 31)) return false;
+  for (const TileMap* m : {&d.tA, &d.tB})
+    for (int b = 0; b < m->nbits; ++b) {
+      if (b < 4 && (m->role[b] != 2 || m->gpos[b] != b || m->cbit[b] != b)) return false;
+      if (b >= 4 && m->gpos[b] > 28) return false;
+    }
+  return ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B)) & 15) == 0 &&
+         ((d.sA_s | d.sA_b | d.sB_s | d.sB_b) & 1) == 0;
+}
+
+// ---------------------------------------------------------------------------
 // Long sums (K >= 256): one tile per workgroup, three workgroups per CU.  The
 // per-tile overheads the persistent walk hides are small against hundreds of
 // chunks, and the third resident wave per SIMD keeps the matrix cores busier
@@ -489,10 +835,19 @@ hipError_t launch_mfma32_kernel(const StepDesc& d, int sa, int sb, int sc, dim3 
                                 hipStream_t s) {
   if (d.rt != 7 || d.nt != 6 || d.kt != 4) return hipErrorInvalidValue;
   const uint64_t n_items = (uint64_t)grid.x * (uint64_t)d.copies;
-  // Sums of 256 or more complex terms: one tile per workgroup (grid = tiles
-  // x copies as given); shorter sums: the persistent walk.
+  // Operands that can be copied straight into LDS: k_mfma32_copy at every length
+  // of the sum (figures there; the smallest calls, 2^(9+6) x 2^(7+6), take 25 us
+  // either way).  Others, sums of 256 or more complex terms: one tile per
+  // workgroup (grid = tiles x copies as given); shorter sums: the persistent walk.
   const bool tiles_kernel = d.variant & kVarTiles ? true : (d.variant & kVarPersistent ? false : d.n_ko >= 4);
   const bool m3 = (d.variant & kVar4M) == 0;
+  if (!(d.variant & kVarTiles) && m3 && copy_fits(d, sa, sb, n_items)) {
+    grid = dim3((unsigned)(n_items < kMfmaGrid ? n_items : kMfmaGrid), 1);
+    if (sc == ST_F16) hipLaunchKernelGGL(k_mfma32_copy<ST_F16>, grid, dim3(256), 0, s, d, (uint32_t)n_items);
+    else if (sc == ST_BF16) hipLaunchKernelGGL(k_mfma32_copy<ST_BF16>, grid, dim3(256), 0, s, d, (uint32_t)n_items);
+    else hipLaunchKernelGGL(k_mfma32_copy<ST_C64>, grid, dim3(256), 0, s, d, (uint32_t)n_items);
+    return hipGetLastError();
+  }
   if (!tiles_kernel) grid = dim3((unsigned)(n_items < kMfmaGrid ? n_items : kMfmaGrid), 1);
   RQC_MFMA_CASE(ST_C64, ST_C64, ST_C64)
   RQC_MFMA_CASE(ST_C64, ST_C64, ST_F16)

@@ -161,8 +161,9 @@ hipError_t launch_chain(const ChainArgs& a, int n_comps, int max_copies, int lds
 // Kernel variant bits of a step (StepDesc::variant).  FP32 matrix-core
 // kernel: the complex products as four real products on the real expansion
 // of B (kVar4M) or as three (the default); one tile per workgroup
-// (kVarTiles) or the persistent walk (kVarPersistent); neither: per-tile for
-// sums of 256 or more.
+// (kVarTiles) or the persistent walk (kVarPersistent); neither: the walk where
+// the operands can be copied straight into LDS, else per-tile for sums of 256
+// or more.
 // Any kernel: kVarFP32Math keeps the arithmetic in FP32 on 16-bit stored
 // operands (the row kernel would otherwise use the 16-bit matrix cores).
 // 16-bit matrix-core kernel: kVarStream streams A past a resident B tile

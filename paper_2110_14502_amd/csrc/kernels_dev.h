@@ -153,6 +153,23 @@ __device__ __forceinline__ Scale compute_scale(const StepDesc& d, int js, int jb
   return scale_of(d, load_scale(d, js, jb));
 }
 
+// compute_scale with scalar loads, for uniform js, jb and values that this
+// launch does not write (its inputs'): they do not wait for the vector loads,
+// copies and stores in flight.
+__device__ __forceinline__ Scale compute_scale_s(const StepDesc& d, int js, int jb) {
+  if (!d.track) return Scale{0, 0};
+  using CI = const __attribute__((address_space(4))) int*;
+  using CF = const __attribute__((address_space(4))) float*;
+  const int iA = __builtin_amdgcn_readfirstlane(js * d.eA_s + jb * d.eA_b);
+  const int iB = __builtin_amdgcn_readfirstlane(js * d.eB_s + jb * d.eB_b);
+  ScaleIn r;
+  r.eA = d.expA ? ((CI)(uintptr_t)d.expA)[iA] : 0;
+  r.eB = d.expB ? ((CI)(uintptr_t)d.expB)[iB] : 0;
+  r.mA = d.maxA ? ((CF)(uintptr_t)d.maxA)[iA] : d.maxA_const;
+  r.mB = d.maxB ? ((CF)(uintptr_t)d.maxB)[iB] : d.maxB_const;
+  return scale_of(d, r);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
@@ -270,6 +287,37 @@ __device__ __forceinline__ void k_offsets(const StepDesc& d, const OuterTab& o, 
     }
 }
 
+// The same address bits held in registers, lane i the ones of outer bit i; the
+// bits of a (uniform) index are read out by lane, a few scalar instructions
+// each, where the table costs an LDS round trip per bit.
+struct OuterReg {
+  uint32_t rn, k;  // bytes: ro_A, ro_C, no_B, no_C; ko_A, ko_B
+};
+static_assert(kMaxOuter <= 64, "one lane per outer bit");
+
+__device__ __forceinline__ OuterReg outer_reg(const StepDesc& d) {
+  const int i = threadIdx.x & 63;
+  OuterReg o{0, 0};
+  if (i < kMaxOuter) {
+    o.rn = (uint32_t)(uint8_t)d.ro_A[i] | (uint32_t)(uint8_t)d.ro_C[i] << 8 |
+           (uint32_t)(uint8_t)d.no_B[i] << 16 | (uint32_t)(uint8_t)d.no_C[i] << 24;
+    o.k = (uint32_t)(uint8_t)d.ko_A[i] | (uint32_t)(uint8_t)d.ko_B[i] << 8;
+  }
+  return o;
+}
+
+// Sum of 2^(byte 0 of lane i) and of 2^(byte 1 of lane i) over the bits i of m
+// (uniform).
+__device__ __forceinline__ void outer_sum(uint32_t v, uint32_t m, int64_t& x, int64_t& y) {
+  while (m) {
+    const int i = __builtin_ctz(m);
+    m &= m - 1;
+    const uint32_t w = __builtin_amdgcn_readlane(v, i);
+    x += int64_t(1) << (w & 255);
+    y += int64_t(1) << ((w >> 8) & 255);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Offset tables of a tile: element e (bits in increasing address order) sits
 // at global offset g_lo[e & 63] + g_hi[e >> 6] and at LDS coordinate
@@ -362,6 +410,51 @@ __device__ __forceinline__ void store_out4(const StepDesc& d, int64_t at, float2
   if (d.track) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      const float2 r = round_c<SC>(v[i]);
+      const float m = fmaxf(fabsf(r.x), fabsf(r.y));
+      if (!(m <= 3.4e38f)) bad = 1;
+      else lmax = fmaxf(lmax, m);
+    }
+  }
+}
+
+// Two elements at consecutive addresses (at: the first, even): one 16-byte
+// (complex64) or 8-byte store, so that a wave's lanes write consecutive bytes.
+template <int SC>
+__device__ __forceinline__ void store_out2(const StepDesc& d, int64_t at, float2 (&v)[2],
+                                           const Scale& sc, float& lmax, int& bad) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (sc.shift) {
+      v[i].x = ldexpf(v[i].x, -sc.shift);
+      v[i].y = ldexpf(v[i].y, -sc.shift);
+    }
+  }
+  if (SC == ST_C64) {
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    f4v w = {v[0].x, v[0].y, v[1].x, v[1].y};
+    *reinterpret_cast<f4v*>(reinterpret_cast<float2*>(d.C) + at) = w;
+  } else {
+    uint32_t w[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (SC == ST_F16) {
+        h2 o;
+        o.x = (_Float16)v[i].x;
+        o.y = (_Float16)v[i].y;
+        w[i] = __builtin_bit_cast(uint32_t, o);
+      } else {
+        b2 o;
+        o.x = (__bf16)v[i].x;
+        o.y = (__bf16)v[i].y;
+        w[i] = __builtin_bit_cast(uint32_t, o);
+      }
+    }
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(d.C) + at) = make_uint2(w[0], w[1]);
+  }
+  if (d.track) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
       const float2 r = round_c<SC>(v[i]);
       const float m = fmaxf(fabsf(r.x), fabsf(r.y));
       if (!(m <= 3.4e38f)) bad = 1;
@@ -481,6 +574,36 @@ __device__ __forceinline__ void store_half4(const StepDesc& d, const float* Cs, 
     for (int i = 0; i < 4; ++i) x[j][i] = make_float2(Cs[lo4[i] + c[j]], Cs[lo4[i] + c[j] + 1]);
 #pragma unroll
   for (int j = 0; j < 4; ++j) store_out4<SC>(d, base + g[j], x[j], sc, lmax, bad);
+}
+
+// 16 bytes per lane from memory to LDS: lane i's go to LDS byte dst + 16 i (dst
+// uniform).  In assembly because the compiler waits for every copy in flight
+// before any LDS read when it places the waits itself; the kernel waits for its
+// copies (vmcnt) and meets a barrier before it reads them.  No vector register
+// is written; M0, the LDS address, has no other use in these kernels and must
+// be set one wait state ahead.
+__device__ __forceinline__ void lds_copy16(const void* src, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
+                   __builtin_amdgcn_readfirstlane(dst)),
+               "v"(src)
+               : "memory");
+}
+// The same from base (uniform) + off: no vector address arithmetic.
+__device__ __forceinline__ void lds_copy16(const void* base, uint32_t off, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(
+                   __builtin_amdgcn_readfirstlane(dst)),
+               "v"(off), "s"(base)
+               : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+// A workgroup barrier without the waits of __syncthreads (the caller places
+// them); memory accesses stay on their side.
+__device__ __forceinline__ void plain_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Per-kernel launchers (one translation unit each).
