@@ -342,15 +342,16 @@ __device__ __forceinline__ float2 word_c(uint32_t w) {
   }
 }
 
-template <int RT, int NT, int S>
-__global__ __launch_bounds__(kSimtBlock) void k_dot(StepDesc d) {
-  constexpr int M = 1 << RT, N = 1 << NT, LOGN = RT + NT, NOUT = M * N;
-  constexpr int G = S == ST_C64 ? 2 : 4;  // complex values per 16-byte load
-  constexpr int EB = S == ST_C64 ? 8 : 4;  // bytes per complex value
-  __shared__ int64_t coff[NOUT];
-  __shared__ float2 wsum[kSimtBlock / 64][NOUT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < NOUT; i += kSimtBlock) {
+typedef float dot_f4 __attribute__((ext_vector_type(4)));
+typedef unsigned int dot_u4 __attribute__((ext_vector_type(4)));
+
+// Offsets of the rows of A and the columns of B and of the outputs in C (coff:
+// shared, 2^(RT + NT) entries); the same in every thread, so the compiler keeps
+// the first two in scalar registers.
+template <int M, int N>
+__device__ __forceinline__ void dot_offsets(const StepDesc& d, int64_t (&arow)[M], int64_t (&bcol)[N],
+                                            int64_t* coff) {
+  for (int i = threadIdx.x; i < M * N; i += kSimtBlock) {
     int64_t c = 0;  // C offset of output i = r * N + n
     for (int x = 0; x < d.tC.nbits; ++x) {
       const int v = d.tC.role[x] == 0 ? i / N : i % N;
@@ -358,9 +359,6 @@ __global__ __launch_bounds__(kSimtBlock) void k_dot(StepDesc d) {
     }
     coff[i] = c;
   }
-  // Offsets of the rows of A and the columns of B (the same in every
-  // thread, so the compiler keeps them in scalar registers).
-  int64_t arow[M], bcol[N];
 #pragma unroll
   for (int i = 0; i < M; ++i) {
     arow[i] = 0;
@@ -373,105 +371,218 @@ __global__ __launch_bounds__(kSimtBlock) void k_dot(StepDesc d) {
     for (int x = 0; x < d.tB.nbits; ++x)
       if (d.tB.role[x] == 1 && ((j >> d.tB.cbit[x]) & 1)) bcol[j] += int64_t(1) << d.tB.gpos[x];
   }
+}
+
+// Adds the products of one 16-byte group of every row and column.
+template <int M, int N, int S>
+__device__ __forceinline__ void dot_add(const dot_u4 (&a)[M], const dot_u4 (&b)[N], float (&ax)[M * N],
+                                        float (&ay)[M * N]) {
+  constexpr int NOUT = M * N;
+  if constexpr (S == ST_C64) {
+#pragma unroll
+    for (int o = 0; o < NOUT; ++o) {
+      const dot_f4 x = __builtin_bit_cast(dot_f4, a[o / N]);
+      const dot_f4 y = __builtin_bit_cast(dot_f4, b[o % N]);
+      ax[o] += x[0] * y[0] - x[1] * y[1] + x[2] * y[2] - x[3] * y[3];
+      ay[o] += x[0] * y[1] + x[1] * y[0] + x[2] * y[3] + x[3] * y[2];
+    }
+  } else {
+    float2 bf[N][4];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bf[j][q] = word_c<S>(b[j][q]);
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      float2 af[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) af[q] = word_c<S>(a[i][q]);
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const int o = i * N + j;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          ax[o] += af[q].x * bf[j][q].x - af[q].y * bf[j][q].y;
+          ay[o] += af[q].x * bf[j][q].y + af[q].y * bf[j][q].x;
+        }
+      }
+    }
+  }
+}
+
+// Sums the outputs over the workgroup and writes split `split`'s partial.
+template <int LOGN, int NOUT>
+__device__ __forceinline__ void dot_finish(const StepDesc& d, float (&ax)[NOUT], float (&ay)[NOUT],
+                                           float2 (&wsum)[kSimtBlock / 64][NOUT], const int64_t* coff,
+                                           int split, int64_t oC) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // Recursive halving over the wave: at offset s a lane keeps the lower
+  // or upper half of its outputs ((lane & s) set: upper) and adds the
+  // partner's copy of that half.
+  // The step counter t is the unrolled induction variable, so every count
+  // and index below is a compile-time constant (a run-time index would put
+  // the output arrays in scratch memory).
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    const int s = 32 >> t;
+    const int c = NOUT >> t;  // outputs a lane holds before this step
+    if (c > 1) {
+      const int h = c >> 1;
+      const bool up = (lane & s) != 0;
+#pragma unroll
+      for (int o = 0; o < NOUT / 2; ++o) {
+        if (o < h) {
+          // (Values, not references, are selected: a selected address would
+          // put the arrays in scratch memory, too.)
+          const float lx = ax[o], ux = ax[o + h], ly = ay[o], uy = ay[o + h];
+          const float sx = up ? lx : ux, sy = up ? ly : uy;
+          const float kx = up ? ux : lx, ky = up ? uy : ly;
+          ax[o] = kx + __shfl_xor(sx, s, 64);
+          ay[o] = ky + __shfl_xor(sy, s, 64);
+        }
+      }
+    } else {
+      ax[0] += __shfl_xor(ax[0], s, 64);
+      ay[0] += __shfl_xor(ay[0], s, 64);
+    }
+  }
+  // Lane l holds output l >> (6 - LOGN).
+  if ((lane & ((64 >> LOGN) - 1)) == 0) wsum[wave][lane >> (6 - LOGN)] = make_float2(ax[0], ay[0]);
+  __syncthreads();
+  if (tid < NOUT) {
+    float sx = 0.f, sy = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSimtBlock / 64; ++w) {
+      sx += wsum[w][tid].x;
+      sy += wsum[w][tid].y;
+    }
+    d.P[(int64_t)split * d.p_stride + oC + coff[tid]] = make_float2(sx, sy);
+  }
+  __syncthreads();
+}
+
+template <int RT, int NT, int S>
+__global__ __launch_bounds__(kSimtBlock, 2) void k_dot(StepDesc d) {
+  constexpr int M = 1 << RT, N = 1 << NT, LOGN = RT + NT, NOUT = M * N;
+  constexpr int G = S == ST_C64 ? 2 : 4;  // complex values per 16-byte load
+  constexpr int EB = S == ST_C64 ? 8 : 4;  // bytes per complex value
+  __shared__ int64_t coff[NOUT];
+  __shared__ float2 wsum[kSimtBlock / 64][NOUT];
+  const int tid = threadIdx.x;
+  int64_t arow[M], bcol[N];
+  dot_offsets<M, N>(d, arow, bcol, coff);
   __syncthreads();
   const int64_t Ks = int64_t(1) << (d.k_total - d.ksplit);
   const int64_t k0 = (int64_t)blockIdx.x * Ks;
-  typedef float f4v __attribute__((ext_vector_type(4)));
-  typedef unsigned int u4v __attribute__((ext_vector_type(4)));
   for (int copy = blockIdx.y; copy < d.copies; copy += gridDim.y) {
     const int js = copy % d.gs_c, jb = copy / d.gs_c;
     const int64_t oA = js * d.sA_s + jb * d.sA_b, oB = js * d.sB_s + jb * d.sB_b;
     const int64_t oC = js * d.sC_s + jb * d.sC_b;
     // Row i of A from summed index k0 on, in 16-byte groups of G values.
-    const u4v* pa[M];
-    const u4v* pb[N];
+    const dot_u4* pa[M];
+    const dot_u4* pb[N];
 #pragma unroll
     for (int i = 0; i < M; ++i)
-      pa[i] = reinterpret_cast<const u4v*>(static_cast<const char*>(d.A) + EB * (oA + arow[i] + k0));
+      pa[i] = reinterpret_cast<const dot_u4*>(static_cast<const char*>(d.A) + EB * (oA + arow[i] + k0));
 #pragma unroll
     for (int j = 0; j < N; ++j)
-      pb[j] = reinterpret_cast<const u4v*>(static_cast<const char*>(d.B) + EB * (oB + bcol[j] + k0));
+      pb[j] = reinterpret_cast<const dot_u4*>(static_cast<const char*>(d.B) + EB * (oB + bcol[j] + k0));
     float ax[NOUT], ay[NOUT];
 #pragma unroll
     for (int o = 0; o < NOUT; ++o) ax[o] = ay[o] = 0.f;
     const int ngroup = (int)(Ks / G);
     for (int p = tid; p < ngroup; p += kSimtBlock) {
-      u4v a[M], b[N];
+      dot_u4 a[M], b[N];
 #pragma unroll
       for (int i = 0; i < M; ++i) a[i] = pa[i][p];
 #pragma unroll
       for (int j = 0; j < N; ++j) b[j] = pb[j][p];
-      if constexpr (S == ST_C64) {
-#pragma unroll
-        for (int o = 0; o < NOUT; ++o) {
-          const f4v x = __builtin_bit_cast(f4v, a[o / N]);
-          const f4v y = __builtin_bit_cast(f4v, b[o % N]);
-          ax[o] += x[0] * y[0] - x[1] * y[1] + x[2] * y[2] - x[3] * y[3];
-          ay[o] += x[0] * y[1] + x[1] * y[0] + x[2] * y[3] + x[3] * y[2];
-        }
-      } else {
-        float2 bf[N][4];
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) bf[j][q] = word_c<S>(b[j][q]);
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-          float2 af[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) af[q] = word_c<S>(a[i][q]);
-#pragma unroll
-          for (int j = 0; j < N; ++j) {
-            const int o = i * N + j;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              ax[o] += af[q].x * bf[j][q].x - af[q].y * bf[j][q].y;
-              ay[o] += af[q].x * bf[j][q].y + af[q].y * bf[j][q].x;
-            }
-          }
-        }
-      }
+      dot_add<M, N, S>(a, b, ax, ay);
     }
-    // Recursive halving over the wave: at offset s a lane keeps the lower
-    // or upper half of its outputs ((lane & s) set: upper) and adds the
-    // partner's copy of that half.
-    // The step counter t is the unrolled induction variable, so every count
-    // and index below is a compile-time constant (a run-time index would put
-    // the output arrays in scratch memory).
+    dot_finish<LOGN>(d, ax, ay, wsum, coff, blockIdx.x, oC);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same sums, in the same order, with the reads kept in flight: with 16 or
+// more outputs the accumulators leave no registers for a second set of loads,
+// so k_dot alternates between waiting for memory and multiplying (63 % of the
+// wave cycles waiting).  Here each wave copies its next groups straight into LDS
+// (a private area, no barriers) while it multiplies the ones it has read from
+// there, across splits and copies as well: the workgroups are persistent (two
+// per CU), and the next item's first groups are in flight while an item's
+// outputs are combined.
+// 65 KB of LDS for 8 x 8 outputs.  Measured, 8 x 8 outputs of 2^18 terms, 32
+// copies: complex64 1.07 GB in 320 -> 205 us (5.2 TB/s; a copy of the card
+// reads 2.4 and writes 2.4), FP16 0.54 GB in 275 -> 187 us (then bound by the
+// multiply-adds and conversions).
+// ---------------------------------------------------------------------------
+constexpr unsigned kDotGrid = 256 * 2;
+
+template <int RT, int NT, int S>
+__global__ __launch_bounds__(kSimtBlock, 2) void k_dot_copy(StepDesc d, uint32_t n_items) {
+  constexpr int M = 1 << RT, N = 1 << NT, LOGN = RT + NT, NOUT = M * N;
+  constexpr int G = S == ST_C64 ? 2 : 4, EB = S == ST_C64 ? 8 : 4;
+  __shared__ __attribute__((aligned(16))) char lds[kSimtBlock / 64][M + N][1024];
+  __shared__ int64_t coff[NOUT];
+  __shared__ float2 wsum[kSimtBlock / 64][NOUT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int64_t arow[M], bcol[N];
+  dot_offsets<M, N>(d, arow, bcol, coff);
+  __syncthreads();
+  const int lg = d.k_total - d.ksplit;
+  const int n_it = (1 << lg) / (G * kSimtBlock);
+  const uint32_t smask = (1u << d.ksplit) - 1, step = gridDim.x;
+  const uint32_t l0 = lds_address(&lds[wave][0][0]);
+
+  // The next groups to copy: group `fp` of item `fi`.
+  uint32_t fi = blockIdx.x;
+  int fp = 0;
+  const char *fA = nullptr, *fB = nullptr;
+  auto seek = [&]() {
+    if (fi >= n_items) return;
+    const int copy = (int)(fi >> d.ksplit), js = copy % d.gs_c, jb = copy / d.gs_c;
+    const int64_t k0 = (int64_t)(fi & smask) << lg;
+    fA = static_cast<const char*>(d.A) + EB * (js * d.sA_s + jb * d.sA_b + k0);
+    fB = static_cast<const char*>(d.B) + EB * (js * d.sB_s + jb * d.sB_b + k0);
+  };
+  auto fetch = [&]() {
+    if (fi >= n_items) return;
+    const uint32_t off = (uint32_t)(fp * kSimtBlock + tid) * 16;
 #pragma unroll
-    for (int t = 0; t < 6; ++t) {
-      const int s = 32 >> t;
-      const int c = NOUT >> t;  // outputs a lane holds before this step
-      if (c > 1) {
-        const int h = c >> 1;
-        const bool up = (lane & s) != 0;
+    for (int i = 0; i < M; ++i) lds_copy16(fA + EB * arow[i], off, l0 + (uint32_t)(i * 1024));
 #pragma unroll
-        for (int o = 0; o < NOUT / 2; ++o) {
-          if (o < h) {
-            const float sx = up ? ax[o] : ax[o + h], sy = up ? ay[o] : ay[o + h];
-            const float kx = up ? ax[o + h] : ax[o], ky = up ? ay[o + h] : ay[o];
-            ax[o] = kx + __shfl_xor(sx, s, 64);
-            ay[o] = ky + __shfl_xor(sy, s, 64);
-          }
-        }
-      } else {
-        ax[0] += __shfl_xor(ax[0], s, 64);
-        ay[0] += __shfl_xor(ay[0], s, 64);
-      }
+    for (int j = 0; j < N; ++j) lds_copy16(fB + EB * bcol[j], off, l0 + (uint32_t)((M + j) * 1024));
+    if (++fp == n_it) {
+      fp = 0;
+      fi += step;
+      seek();
     }
-    // Lane l holds output l >> (6 - LOGN).
-    if ((lane & ((64 >> LOGN) - 1)) == 0) wsum[wave][lane >> (6 - LOGN)] = make_float2(ax[0], ay[0]);
-    __syncthreads();
-    if (tid < NOUT) {
-      float sx = 0.f, sy = 0.f;
+  };
+  seek();
+  fetch();
+  for (uint32_t item = blockIdx.x; item < n_items; item += step) {
+    float ax[NOUT], ay[NOUT];
 #pragma unroll
-      for (int w = 0; w < kSimtBlock / 64; ++w) {
-        sx += wsum[w][tid].x;
-        sy += wsum[w][tid].y;
-      }
-      d.P[(int64_t)blockIdx.x * d.p_stride + oC + coff[tid]] = make_float2(sx, sy);
+    for (int o = 0; o < NOUT; ++o) ax[o] = ay[o] = 0.f;
+    for (int it = 0; it < n_it; ++it) {
+      // This wave's copies have landed; once they are in registers, the area is
+      // free for the next ones.
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      asm volatile("" ::: "memory");
+      dot_u4 a[M], b[N];
+#pragma unroll
+      for (int i = 0; i < M; ++i) a[i] = *reinterpret_cast<const dot_u4*>(&lds[wave][i][lane * 16]);
+#pragma unroll
+      for (int j = 0; j < N; ++j) b[j] = *reinterpret_cast<const dot_u4*>(&lds[wave][M + j][lane * 16]);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      fetch();
+      dot_add<M, N, S>(a, b, ax, ay);
     }
-    __syncthreads();
+    const int copy = (int)(item >> d.ksplit), js = copy % d.gs_c, jb = copy / d.gs_c;
+    dot_finish<LOGN>(d, ax, ay, wsum, coff, (int)(item & smask), js * d.sC_s + jb * d.sC_b);
   }
 }
 
@@ -490,13 +601,36 @@ static bool dot_fits(const StepDesc& d, int sa, int sb, uint64_t tiles) {
   return true;
 }
 
+// Whether k_dot_copy takes it: 16 outputs or more (below, k_dot has registers
+// for twice the waves), whole rounds of the workgroup, and rows that start on
+// 16-byte boundaries within 32-bit offsets.
+static bool dot_copies(const StepDesc& d, int sa) {
+  const int lg = d.k_total - d.ksplit, g = sa == ST_C64 ? 1 : 2;
+  if (d.rt + d.nt < 4 || lg < g + 8 || lg > 28 || (uint64_t(d.copies) << d.ksplit) >= (1u << 30)) return false;
+  if ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B)) & 15) return false;
+  return ((d.sA_s | d.sA_b | d.sB_s | d.sB_b) & ((1 << g) - 1)) == 0;
+}
+
+template <int RT, int NT, int S>
+static void launch_dot_nt(const StepDesc& d, dim3 grid, hipStream_t s) {
+  if constexpr (RT + NT >= 4) {
+    if (dot_copies(d, S)) {
+      const uint32_t n = (uint32_t)d.copies << d.ksplit;
+      hipLaunchKernelGGL((k_dot_copy<RT, NT, S>), dim3(n < kDotGrid ? n : kDotGrid), dim3(kSimtBlock), 0, s,
+                         d, n);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_dot<RT, NT, S>), grid, dim3(kSimtBlock), 0, s, d);
+}
+
 template <int RT, int S>
 static void launch_dot_rt(const StepDesc& d, dim3 grid, hipStream_t s) {
   switch (d.nt) {
-    case 0: hipLaunchKernelGGL((k_dot<RT, 0, S>), grid, dim3(kSimtBlock), 0, s, d); break;
-    case 1: hipLaunchKernelGGL((k_dot<RT, 1, S>), grid, dim3(kSimtBlock), 0, s, d); break;
-    case 2: hipLaunchKernelGGL((k_dot<RT, 2, S>), grid, dim3(kSimtBlock), 0, s, d); break;
-    default: hipLaunchKernelGGL((k_dot<RT, 3, S>), grid, dim3(kSimtBlock), 0, s, d); break;
+    case 0: launch_dot_nt<RT, 0, S>(d, grid, s); break;
+    case 1: launch_dot_nt<RT, 1, S>(d, grid, s); break;
+    case 2: launch_dot_nt<RT, 2, S>(d, grid, s); break;
+    default: launch_dot_nt<RT, 3, S>(d, grid, s); break;
   }
 }
 
