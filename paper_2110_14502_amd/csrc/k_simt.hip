@@ -504,10 +504,10 @@ __global__ __launch_bounds__(kSimtBlock, 2) void k_dot(StepDesc d) {
 }
 
 // ---------------------------------------------------------------------------
-// The same sums, in the same order, with the reads kept in flight: with 16 or
-// more outputs the accumulators leave no registers for a second set of loads,
-// so k_dot alternates between waiting for memory and multiplying (63 % of the
-// wave cycles waiting).  Here each wave copies its next groups straight into LDS
+// The same sums, in the same order, with the reads kept in flight: beside many
+// accumulators there are no registers for a second set of loads, so k_dot
+// alternates between waiting for memory and multiplying (63 % of the wave
+// cycles waiting, with 64 outputs).  Here each wave copies its next groups straight into LDS
 // (a private area, no barriers) while it multiplies the ones it has read from
 // there, across splits and copies as well: the workgroups are persistent (two
 // per CU), and the next item's first groups are in flight while an item's
@@ -515,7 +515,9 @@ __global__ __launch_bounds__(kSimtBlock, 2) void k_dot(StepDesc d) {
 // 65 KB of LDS for 8 x 8 outputs.  Measured, 8 x 8 outputs of 2^18 terms, 32
 // copies: complex64 1.07 GB in 320 -> 205 us (5.2 TB/s; a copy of the card
 // reads 2.4 and writes 2.4), FP16 0.54 GB in 275 -> 187 us (then bound by the
-// multiply-adds and conversions).
+// multiply-adds and conversions).  Smaller outputs gain less: 8 x 1 of 2^16
+// terms 57 -> 44 us, 4 x 2 36 -> 32, 2 x 1 of 2^20 145 -> 143; more workgroups
+// where the LDS allows them: 0 to 2 % slower.
 // ---------------------------------------------------------------------------
 constexpr unsigned kDotGrid = 256 * 2;
 
@@ -601,19 +603,19 @@ static bool dot_fits(const StepDesc& d, int sa, int sb, uint64_t tiles) {
   return true;
 }
 
-// Whether k_dot_copy takes it: 16 outputs or more (below, k_dot has registers
-// for twice the waves), whole rounds of the workgroup, and rows that start on
-// 16-byte boundaries within 32-bit offsets.
+// Whether k_dot_copy takes it: whole rounds of the workgroup, and rows that
+// start on 16-byte boundaries within 32-bit offsets.  (A single output, 102 us
+// for 2^20 terms either way, stays with k_dot.)
 static bool dot_copies(const StepDesc& d, int sa) {
   const int lg = d.k_total - d.ksplit, g = sa == ST_C64 ? 1 : 2;
-  if (d.rt + d.nt < 4 || lg < g + 8 || lg > 28 || (uint64_t(d.copies) << d.ksplit) >= (1u << 30)) return false;
+  if (lg < g + 8 || lg > 28 || (uint64_t(d.copies) << d.ksplit) >= (1u << 30)) return false;
   if ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B)) & 15) return false;
   return ((d.sA_s | d.sA_b | d.sB_s | d.sB_b) & ((1 << g) - 1)) == 0;
 }
 
 template <int RT, int NT, int S>
 static void launch_dot_nt(const StepDesc& d, dim3 grid, hipStream_t s) {
-  if constexpr (RT + NT >= 4) {
+  if constexpr (RT + NT >= 1) {
     if (dot_copies(d, S)) {
       const uint32_t n = (uint32_t)d.copies << d.ksplit;
       hipLaunchKernelGGL((k_dot_copy<RT, NT, S>), dim3(n < kDotGrid ? n : kDotGrid), dim3(kSimtBlock), 0, s,

@@ -1,6 +1,6 @@
-"""The streaming dot products with the reads kept in flight (16 to 64 outputs,
+"""The streaming dot products with the reads kept in flight (2 to 64 outputs,
 rows on 16-byte boundaries): one round of the workgroup per split and several,
-fewer splits than workgroups and more, row and column counts from 2 to 8.
+fewer splits than workgroups and more, row and column counts from 1 to 8.
 
 The same operands one element (8 bytes) off such a boundary go to the kernel that
 reads through registers, which sums in the same order: the same bits.  Both are
@@ -26,6 +26,9 @@ CASES = [
     (2, 3, 12, 700),
     (3, 2, 19, 5),
     (3, 3, 21, 1),      # 2^9 splits of 2^12: as many items as workgroups
+    (1, 0, 18, 16),
+    (0, 2, 16, 32),
+    (1, 1, 17, 24),
     (3, 3, 15, 32),     # 2^8 terms per split: the register kernel both times
 ]
 
