@@ -650,16 +650,19 @@ __global__ __launch_bounds__(256, 2) void k_mfma32_copy(StepDesc d, uint32_t n_i
         __builtin_amdgcn_wave_barrier();
         const int64_t at = oC + g_wave + (i ? rw[1] : 0) + (hf ? rw[0] : 0) + g_lo;
         if (vec_c) {
-          float2 x[4][2];
+          float2 x[8];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int c = cc[64 + 2 * u + (lane >> 5)];
-            x[u][0] = Cs[c_lo + c];
-            x[u][1] = Cs[c_lo1 + c];
+            x[2 * u] = Cs[c_lo + c];
+            x[2 * u + 1] = Cs[c_lo1 + c];
           }
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            store_out2<SC>(d, at + cg[64 + 2 * u + (lane >> 5)], x[u], sc, lmax, bad);
+          for (int u = 0; u < 4; ++u) {
+            float2(&pair)[2] = *reinterpret_cast<float2(*)[2]>(&x[2 * u]);
+            store_out2<SC>(d, at + cg[64 + 2 * u + (lane >> 5)], pair, sc);
+          }
+          if (d.track) track_out<SC, 8>(x, lmax, bad);
         } else {
           float2 x[8];
 #pragma unroll

@@ -253,15 +253,15 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
   float lmax = 0.f;
   int bad = 0;
   __syncthreads();  // tables ready
-  const int64_t glo = tc.g[lane];
-  const int32_t clo = tc.c[lane];
-  // Vector stores: this lane's four consecutive low elements (the same for
-  // every group it stores).
-  const int lo4 = (lane & 15) << 2;
-  const int64_t glo4 = tc.g[lo4];
-  int32_t clo4[4];
+  // This lane's low elements (the same for every group it stores): one, or with
+  // vector stores two (complex64) or four consecutive ones, so that a wave's
+  // store writes consecutive bytes.
+  const int lg_e = !d.vec_c ? 0 : d.sc_store == ST_C64 ? 1 : 2;
+  const int lo_e = (lane << lg_e) & 63;
+  const int64_t glo = tc.g[lo_e];
+  int32_t clo[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) clo4[i] = tc.c[lo4 + i];
+  for (int i = 0; i < 4; ++i) clo[i] = tc.c[(lo_e + i) & 63];
   int64_t oA = 0, oB = 0, oC = 0;
   for (; t < t_end; ++t) {
     const uint64_t ro = t & rmask;
@@ -443,7 +443,31 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
         // At most 512 staged elements (64 rows x 8 columns): eight per lane,
         // or two groups of four.  Table and staging reads are issued
         // together before the stores so that their latencies overlap.
-        if (d.vec_c) {
+        if (d.vec_c && d.sc_store == ST_C64) {
+          int64_t g[4];
+          int32_t cc[4];
+          float2 x[4][2];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int v = lane + 64 * u;
+            const int hi = 64 + (v < (nC >> 1) ? (v >> 5) : 0);
+            g[u] = tc.g[hi];
+            cc[u] = tc.c[hi];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const int c = clo[i] + cc[u];
+              x[u][i] = make_float2(Cs[c], Cs[c + 1]);
+            }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (lane + 64 * u >= (nC >> 1)) break;
+            store_out2<ST_C64>(d, oC + gch + glo + g[u], x[u], sc);
+            if (d.track) track_out<ST_C64, 2>(x[u], lmax, bad);
+          }
+        } else if (d.vec_c) {
           int64_t g[2];
           int32_t cc[2];
           float2 x[2][4];
@@ -458,16 +482,15 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
           for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const int c = clo4[i] + cc[u];
+              const int c = clo[i] + cc[u];
               x[u][i] = make_float2(Cs[c], Cs[c + 1]);
             }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             if (lane + 64 * u >= (nC >> 2)) break;
-            const int64_t at = oC + gch + glo4 + g[u];
+            const int64_t at = oC + gch + glo + g[u];
             if (d.sc_store == ST_F16) store_out4<ST_F16>(d, at, x[u], sc, lmax, bad);
-            else if (d.sc_store == ST_BF16) store_out4<ST_BF16>(d, at, x[u], sc, lmax, bad);
-            else store_out4<ST_C64>(d, at, x[u], sc, lmax, bad);
+            else store_out4<ST_BF16>(d, at, x[u], sc, lmax, bad);
           }
         } else {
           int64_t g[8];
@@ -478,7 +501,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
             const int e = lane + 64 * u;
             const int hi = 64 + (e < nC ? (e >> 6) : 0);
             g[u] = tc.g[hi];
-            cc[u] = clo + tc.c[hi];
+            cc[u] = clo[0] + tc.c[hi];
           }
 #pragma unroll
           for (int u = 0; u < 8; ++u) x[u] = make_float2(Cs[cc[u]], Cs[cc[u] + 1]);
