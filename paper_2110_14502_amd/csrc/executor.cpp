@@ -300,6 +300,31 @@ bool step_lp_store(const rqc_plan* p, int prec, size_t i) {
   return prec == RQC_BF16 ? st.lp_bf16 : st.lp;
 }
 
+// The form of the 16-bit matrix kernel for a step with a 16-bit stored A that
+// was not tuned (the sums are the same in all of them: the same bits).
+// Measured in FP16, us, 32 copies, two output orders each; (m, n, k): default /
+// streamed / exchanged:
+//   B complex64 (converted once per tile by the streamed form, per chunk by
+//   the others): (18, 6, 5) 1066 / 948; (16, 6, 6) 337 / 307; (14, 6, 6) 81 / 83;
+//   (15, 7, 5) 233 / 192 / 231; (14, 8, 6) 332 / 303 / 293; k = 7: (16, 7, 7)
+//   844 / 814 / 789 (as a step of a 6x6 call 807 / - / 853), (14, 8, 7) 384 /
+//   377 / 393, (13, 7, 7) 102 / 106 / 104.  So streamed up to k = 6; at k = 7 no
+//   form is better on all orders.
+//   B in 16 bits: (16, 7, 7) 797 / 820 / 689; (16, 7, 5) 528 / 475 / 409;
+//   (13, 7, 7) 93 / 104 / 93; (14, 8, 6) 265 / 260 / 260.  So exchanged where B
+//   fills a row tile; below, (18, 6, 5) 1020 / 948, (14, 6, 5) 64 / 62, (17, 6,
+//   6) 609 / 597, (14, 6, 6) 77 / 82: streamed at k = 5, at k = 6 from 2^16 rows.
+static int32_t mfma16_variant(const rqc_plan* p, int prec, const Step& st) {
+  auto lp = [&](int node) {
+    const int i = p->pd.step_of_node[node];
+    return i >= 0 && !p->pd.steps[i].invariant && step_lp_store(p, prec, (size_t)i);
+  };
+  if (!lp(st.a) || st.k < 5 || st.m < 13) return 0;
+  if (!lp(st.b)) return st.k <= 6 ? kVarStream : 0;
+  if (st.n >= 7) return st.m > st.n ? kVarSwap : 0;
+  return st.k == 5 || (st.k == 6 && st.m >= 16) ? kVarStream : 0;
+}
+
 void select_steps(rqc_plan* p) {
   const PlanData& pd = p->pd;
   const bool storage_only = pd.opts.precision_policy == RQC_POLICY_STORAGE;
@@ -325,7 +350,13 @@ void select_steps(rqc_plan* p) {
           var &= ~kVarSwap;
         }
       } else {
-        var &= ~kVarSwap;
+        var = k == KERN_MFMA16 ? mfma16_variant(p, m, st) : 0;
+        if (var & kVarSwap) {
+          int ks = k;
+          const StepDesc ds = step_desc(st, ks, var);
+          if (ks == k) d = ds;
+          else var = 0;
+        }
       }
       d.variant = var;
       if (m != RQC_F32 && !lp_math) d.variant |= kVarFP32Math;

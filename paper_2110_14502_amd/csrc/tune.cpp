@@ -84,6 +84,7 @@ std::vector<std::pair<int, int>> candidates(rqc_plan* p, int m, size_t i) {
   // four times (the small one stays in L2).
   if (fp32_mma && st.n >= 7 && st.m > st.n && valid(KERN_MFMA, kVarSwap))
     for (int v : {kVarTiles, kVarPersistent}) add(KERN_MFMA, v | kVarSwap);
+  if (cur == KERN_MFMA16) add(KERN_MFMA16, 0);
   if (cur == KERN_MFMA16 && st.k >= 5 && st.k <= 7) add(KERN_MFMA16, kVarStream);
   // The same exchange on the 16-bit matrix cores: a 128-column output is
   // written in whole 128-column rows (one row tile) instead of half rows.
