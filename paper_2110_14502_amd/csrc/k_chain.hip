@@ -13,10 +13,10 @@ namespace rqc {
 // only the subtree's root is written to memory; subtrees that do not depend
 // on each other run side by side in one launch.  A step inside is bound by
 // the LDS round trips of its chain (descriptor, operands, maximum, barrier),
-// not by bandwidth or arithmetic.  Measured (whole calls): 4x4 256 -> 99 us,
-// 24 bitstrings of a 5x5 circuit 715 -> 334 us, 16 FP16 slices of a 5x5
-// circuit 703 -> 300 us, 32 slices of the 6x6 circuit 10.58 -> 9.70 ms in
-// FP32 and 6.00 -> 5.23 ms in FP16.
+// not by bandwidth or arithmetic.  Measured (whole calls, before / one step
+// after the other / levels side by side): 4x4 256 / 99 / 90 us, 24 bitstrings of
+// a 5x5 circuit 715 / 334 / 303, 16 FP16 slices of a 5x5 circuit 703 / 300 / 274;
+// 32 slices of the 6x6 circuit 10.58 -> 9.70 ms in FP32 and 6.00 -> 5.23 in FP16.
 //
 // The arithmetic is the row kernel's, instruction for instruction (its 16 x 8
 // tiles, its deal of the summed indices over the lanes and its order of

@@ -22,8 +22,8 @@ namespace rqc {
 // through an LDS tile written out in C's own address order.  The tile is the
 // wave's own (64 rows x 8 columns), so the waves of a workgroup do not wait for
 // each other within a copy (a 256-row tile took two workgroup barriers per 8
-// columns: (m, n, k) = (17, 4, 4) x 32 261 us against 242 now, (16, 7, 4) x 32
-// 728 -> 658, 16-bit (16, 7, 4) x 32 476 -> 387).
+// columns: (m, n, k) = (17, 4, 4) x 32 261 -> 242 us, and 239 with whole-line
+// stores; (16, 7, 4) x 32 728 -> 658 and 645; 16-bit (16, 7, 4) x 32 476 -> 387).
 //
 // When A is stored in FP16 / BF16 and a K chunk holds 16 or 32 complex
 // values, the products run on the 16-bit matrix cores instead
