@@ -197,15 +197,19 @@ __global__ __launch_bounds__(512, 1) void k_frag_gemm(FragDesc d) {
   // q - 1 and its second half at its own start, so no wave starts a chunk by
   // waiting for LDS, and the halves of a buffer fall free at different
   // barriers: at chunk q's, the second half of chunk q - 1 (taken by chunk q +
-  // 2) and the first half of chunk q itself (taken by chunk q + 3).  Either
-  // way a copy has two chunks' time to land: the barrier waits for all but the
-  // six copies issued one chunk ago.
+  // 2) and the first half of chunk q itself (taken by chunk q + 3).  Every wave
+  // waits for its own LDS reads before that barrier (lgkmcnt(0); the last ones
+  // were issued twelve and more matrix instructions ago): the first half's are
+  // used only behind it, where other waves already copy into the same bytes.
+  // Either way a copy has two chunks' time to land: the barrier waits for all
+  // but the six copies issued one chunk ago.
   int buf = 0;
   auto plane = [&](int q0, floatx16 (&acc)[2][2]) {
     for (int q = q0; q < q0 + n_kc; ++q) {
-      if (q + 2 < n_q) __builtin_amdgcn_s_waitcnt(0x0F76);  // vmcnt(6)
-      else __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): fewer were issued
-      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");  // the reads above are issued before the wait
+      if (q + 2 < n_q) __builtin_amdgcn_s_waitcnt(0x0076);  // vmcnt(6) lgkmcnt(0)
+      else __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0): fewer copies were issued
+      plain_barrier();
       const int nb = buf == 2 ? 0 : buf + 1;
       frags(buf, 1, a1, b1);
       __builtin_amdgcn_sched_barrier(0);
