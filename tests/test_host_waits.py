@@ -57,3 +57,28 @@ def test_lds_reads_end_before_barriers(source, kernel, n_kernels, tmp_path):
                 # (a lane exchange goes through the LDS unit but not its memory)
                 assert not before.startswith("ds_") or before.startswith("ds_bpermute"), (name, at, before)
     assert found == n_kernels
+
+
+def test_copies_into_lds_name_m0(tmp_path):
+    """lds_copy16 overwrites M0: a value that the compiler keeps there (its own
+    copies into LDS address by M0) has to be set again behind it."""
+    src = tmp_path / "probe.hip"
+    src.write_text("""
+#include "kernels_dev.h"
+using namespace rqc;
+__global__ void probe(const float4* p, float4* out) {
+  __shared__ float4 own[64], other[64];
+  typedef __attribute__((address_space(1))) const void global_t;
+  typedef __attribute__((address_space(3))) void lds_t;
+  __builtin_amdgcn_global_load_lds((global_t*)(p + threadIdx.x), (lds_t*)own, 4, 0, 0);
+  lds_copy16(p + 64 + threadIdx.x, lds_address(other));
+  __builtin_amdgcn_global_load_lds((global_t*)(p + 128 + threadIdx.x), (lds_t*)own, 4, 64, 0);
+  __syncthreads();
+  out[threadIdx.x] = own[threadIdx.x];
+}
+""")
+    (lines,) = [v for k, v in _assembly(str(src), tmp_path).items() if "probe" in k]
+    state = [re.split(r"[ ,]", x)[0] if "global_load_lds" in x else "m0" for x in lines
+             if "global_load_lds" in x or re.match(r"s_mov_b32 m0,", x)]
+    copies = [i for i, x in enumerate(state) if x != "m0"]
+    assert len(copies) == 3 and all(state[i - 1] == "m0" for i in copies), state
