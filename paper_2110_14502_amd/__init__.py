@@ -6,6 +6,7 @@ module fails loudly when the native library has not been built.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import json
 import os
@@ -225,6 +226,16 @@ def _stream_handle(stream=None):
         return C.c_void_p(int(stream))
     import torch
     return C.c_void_p(int(torch.cuda.current_stream().cuda_stream))
+
+
+def _on_stream(stream, device):
+    """Context in which torch allocates for, and copies on, the stream that the
+    call's kernels run on: memory allocated and freed under another stream would
+    be handed out again while they still use it."""
+    import torch
+    if stream is None:
+        return contextlib.nullcontext()
+    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device=device))
 
 
 def _ptr(t):
@@ -569,7 +580,8 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
     if need:
         if workspace is None:
             try:
-                workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
+                with _on_stream(stream, A.device):
+                    workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
             except torch.OutOfMemoryError:
                 if prec != F32:
                     raise
@@ -618,20 +630,21 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     n = amps.numel() // 2
     ns = 0 if samples is None else samples.numel()
     sp = _ptr(samples) if samples is not None else None
-    if n < 1 << 17 and ns < 1 << 17:  # no workspace (rqc.h); asking costs 1 us of 25
-        out = torch.empty(5, dtype=torch.float64, device=amps.device)
-        _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                  _stream_handle(stream)))
-        v = out.cpu().numpy()
-    else:
-        need = C.c_uint64()
-        _check(_lib.rqc_batch_xeb_workspace_bytes(n, ns, C.byref(need)))
-        # The five results, then the workspace (one buffer, so one lifetime).
-        out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
-        _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                     C.c_void_p(out.data_ptr() + 64), need.value,
-                                     _stream_handle(stream)))
-        v = out[:5].cpu().numpy()
+    with _on_stream(stream, amps.device):
+        if n < 1 << 17 and ns < 1 << 17:  # no workspace (rqc.h); asking costs 1 us of 25
+            out = torch.empty(5, dtype=torch.float64, device=amps.device)
+            _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                      _stream_handle(stream)))
+            v = out.cpu().numpy()
+        else:
+            need = C.c_uint64()
+            _check(_lib.rqc_batch_xeb_workspace_bytes(n, ns, C.byref(need)))
+            # The five results, then the workspace (one buffer, so one lifetime).
+            out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
+            _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                         C.c_void_p(out.data_ptr() + 64), need.value,
+                                         _stream_handle(stream)))
+            v = out[:5].cpu().numpy()
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 
