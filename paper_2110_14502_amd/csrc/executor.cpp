@@ -1037,6 +1037,7 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
   r.stream = s;
   r.ws = ws;
   r.ws_bytes = ws_bytes;
+  r.flags_off = W.flags_off;
   r.out = out;
   r.per_slice = per_slice;
   r.gs = gs;
@@ -1051,23 +1052,21 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
     if (sync) hip_check(hipStreamSynchronize(s), "synchronize");
     return;
   }
-  const GroupLayout& L0 = group_layout(p, r.prec, r.gs, r.gb);
-  const WsLayout W0 = ws_layout(p, L0, r.n_ids, r.n_batch);
-  const int64_t nbg = W0.n_bgroups;
+  const int64_t nbg = ((int64_t)r.n_batch + r.gb - 1) / r.gb;
   std::vector<int32_t> flags((size_t)(r.n_ids * nbg));
   if (sync && s == r.stream && flags.size() <= kPinnedFlags) {
     // The flags follow the call on its stream, so that one wait covers both
     // (a blocking copy after the wait takes another 20 us).
     if (!p->pinned_flags)
       hip_check(hipHostMalloc(reinterpret_cast<void**>(&p->pinned_flags), 4 * kPinnedFlags), "flag buffer");
-    hip_check(hipMemcpyAsync(p->pinned_flags, r.ws + W0.flags_off, 4 * flags.size(),
+    hip_check(hipMemcpyAsync(p->pinned_flags, r.ws + r.flags_off, 4 * flags.size(),
                              hipMemcpyDeviceToHost, s),
               "flags");
     hip_check(hipStreamSynchronize(s), "synchronize");
     std::memcpy(flags.data(), p->pinned_flags, 4 * flags.size());
   } else {
     if (sync) hip_check(hipStreamSynchronize(s), "synchronize");
-    hip_check(hipMemcpy(flags.data(), r.ws + W0.flags_off, 4 * flags.size(), hipMemcpyDeviceToHost),
+    hip_check(hipMemcpy(flags.data(), r.ws + r.flags_off, 4 * flags.size(), hipMemcpyDeviceToHost),
               "flags");
   }
   p->last_timing = rqc_timing{};

@@ -78,6 +78,7 @@ struct PendingRun {
   hipStream_t stream = nullptr;
   char* ws = nullptr;
   size_t ws_bytes = 0;
+  int64_t flags_off = 0;       // where this call put its flags (the layout may change before the report)
   double* out = nullptr;
   double* per_slice = nullptr;
   int gs = 1, gb = 1;
