@@ -592,7 +592,10 @@ __device__ __forceinline__ void store_half4(const StepDesc& d, const float* Cs, 
 // uniform).  In assembly because the compiler waits for every copy in flight
 // before any LDS read when it places the waits itself; the kernel waits for its
 // copies (vmcnt) and meets a barrier before it reads them.  No vector register
-// is written; M0, the LDS address, must be set one wait state ahead.
+// is written; M0, the LDS address, must be set one wait state ahead (it is a
+// reserved register, which the compiler points out where it is named as overwritten).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_copy16(const void* src, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
                    __builtin_amdgcn_readfirstlane(dst)),
@@ -606,6 +609,7 @@ __device__ __forceinline__ void lds_copy16(const void* base, uint32_t off, uint3
                "v"(off), "s"(base)
                : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
 }
