@@ -299,13 +299,19 @@ rqc_status rqc_pair_contract(const int32_t* labels_a, int32_t rank_a,
  * 256 x 128, FP32 partial outputs of a split sum (8 bytes per output
  * element per split, summed afterwards in split order).  Also nonzero for
  * RQC_F32 calls (kernel -1) with m >= 8, n >= 7 (or the reverse) and a sum of
- * at least 2^10 terms (2^8 for products of 2^34 multiply-adds and more): then
- * the sum runs on the FP16 matrix cores with every FP32 value split into two
- * FP16 halves and FP32 accumulation, at an error below that of the FP32
- * kernel; the workspace holds the split operands, 12 bytes per element of
- * each operand, and partial outputs of a split sum as above.  An operand that
- * two halves do not represent (a range above 2^18, infinities, NaN) sends the
- * call to the FP32 kernel on the device.  Also nonzero for
+ * at least 2^10 terms (2^8 for products of 2^34 multiply-adds and more), one
+ * product or a batch of up to 64 that is large enough to gain: they may run on
+ * the FP16 matrix cores with every FP32 value split into two FP16 halves (22-23
+ * of its 24 bits) and FP32 accumulation.  The workspace holds the split operands,
+ * 12 bytes per element of each copy of each operand, and partial outputs of a
+ * split sum as above; a call that gains nothing leaves it unused.  The split form
+ * is kept for operands whose every row and column of summed terms is dense and
+ * even; for these its error against 64 bits is 0.4 to 0.8 of the FP32 kernel's on
+ * complex normal values, and up to 1.2 of it where the terms grow along the sum.
+ * All others (few nonzero terms, terms or rows of very different size, equal
+ * terms, real or imaginary operands, infinities, NaN) are told apart on the device and run on the FP32 kernel,
+ * whose results the call then returns bit for bit.  kernel 1 keeps every value and
+ * product in FP32, for all operands.  Also nonzero for
  * RQC_F32 calls that run on the generic kernel (kernel -1 or 0) with output
  * tiles too few to fill the GPU and a long sum: the sum is split over
  * workgroups (as for plan steps) and the workspace holds the complex64
@@ -327,7 +333,8 @@ rqc_status rqc_pair_workspace_bytes(const int32_t* labels_a, int32_t rank_a,
  * FP32 sum on the generic kernel needs a batch's outputs back to back
  * (stride_c = 2^rank_c); with another stride the call runs unsplit.  An FP32
  * call whose split into FP16 halves finds no workspace of the stated size, or
- * operands not 16-byte aligned, runs on the FP32 kernel.  Calls that need no
+ * operands not 16-byte aligned, runs on the FP32 kernel (as rqc_pair_contract
+ * without a workspace does).  Calls that need no
  * workspace behave exactly as rqc_pair_contract. */
 rqc_status rqc_pair_contract_ws(const int32_t* labels_a, int32_t rank_a,
                                 const int32_t* labels_b, int32_t rank_b,

@@ -569,7 +569,9 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
     device).  A call with a long sum takes a two-phase form and needs a
     device workspace (pair_workspace_bytes); one is allocated with torch
     unless `workspace` (a uint8 device tensor) is given.  An FP32 call for
-    which no workspace can be allocated runs without one."""
+    which no workspace can be allocated runs without one.  FP32 long sums of
+    dense, even operands may run on the FP16 matrix cores with every value split
+    into two halves (rqc.h has the bounds); kernel=1 keeps them in FP32."""
     import torch
     prec = PRECISIONS.get(prec, prec) if isinstance(prec, str) else int(prec)
     if C_out is None:

@@ -371,6 +371,30 @@ rqc_status rqc_plan_get_launch_timing(const rqc_plan* p, uint64_t i, rqc_launch_
 
 // ---- single pairwise contraction, permutation, GEMM ---------------------
 
+}  // extern "C"
+
+namespace {
+
+// One batched pairwise step on kernel `kern` (as make_pair_desc takes and sets it).
+rqc::StepDesc pair_desc(const std::vector<int>& la, const std::vector<int>& lb, const std::vector<int>& lc,
+                        int& kern, const void* A, const void* B, void* C, int32_t batch, int64_t stride_a,
+                        int64_t stride_b, int64_t stride_c) {
+  rqc::StepDesc d = rqc::make_pair_desc(la, lb, lc, kern);
+  d.A = A;
+  d.B = B;
+  d.C = C;
+  d.sA_s = stride_a;
+  d.sB_s = stride_b;
+  d.sC_s = stride_c;
+  d.gs_c = batch;
+  d.copies = batch;
+  return d;
+}
+
+}  // namespace
+
+extern "C" {
+
 rqc_status rqc_pair_contract(const int32_t* labels_a, int32_t rank_a, const int32_t* labels_b,
                              int32_t rank_b, const int32_t* labels_c, int32_t rank_c, const void* A,
                              const void* B, void* C, int32_t batch_count, int64_t stride_a,
@@ -394,15 +418,8 @@ rqc_status rqc_pair_contract(const int32_t* labels_a, int32_t rank_a, const int3
   }
   int kern = kernel;
   if (prec != RQC_F32 && (kernel == -1 || kernel == rqc::KERN_MFMA)) kern = rqc::KERN_MFMA16;
-  rqc::StepDesc d = rqc::make_pair_desc(la, lb, lc, kern);
-  d.A = A;
-  d.B = B;
-  d.C = C;
-  d.sA_s = stride_a;
-  d.sB_s = stride_b;
-  d.sC_s = stride_c;
-  d.gs_c = batch_count;
-  d.copies = batch_count;
+  const rqc::StepDesc d =
+      pair_desc(la, lb, lc, kern, A, B, C, batch_count, stride_a, stride_b, stride_c);
   const int lp_kind = prec == RQC_F16 ? rqc::ST_F16 : (prec == RQC_BF16 ? rqc::ST_BF16 : 0);
   rqc::hip_check(rqc::launch_step(d, kern, rqc::ST_C64, rqc::ST_C64, rqc::ST_C64, lp_kind,
                                   static_cast<hipStream_t>(stream)),
@@ -462,30 +479,48 @@ Gemm16Shape gemm16_shape(const std::vector<int>& la, const std::vector<int>& lb,
 }
 
 // FP32 long sums on the FP16 matrix cores (k_split32.hip), automatic kernel
-// choice only.  Taken when the output has at least one 256 x 128 tile (either
-// operand on the row side) and the sum 2^10 terms or more, or 2^8 and the
-// product 2^34 multiply-adds or more.  The FP32 kernel takes 0.15 us per summed
-// term for each round of 512 tiles; this form 90-100 us for its six launches
-// and then a third of the FP32 time: (m, n, k) = (8, 7, 10) 161 -> 96 us, (15,
-// 8, 10) 507 -> 489, (12, 12, 12) 3.70 -> 1.53 ms, (14, 13, 9) 4.31 -> 2.17;
-// below the line (14, 8, 9) 144 -> 158 us, (12, 12, 8) 310 -> 366.
-// Workspaces above 24 GiB (12 bytes per operand element) stay with the FP32
-// kernel, so that the largest steps (rank 32) still fit beside their operands,
-// and so do batches above 64 (the copies run one after the other).
+// choice only: an output of at least one 256 x 128 tile (either operand on the row
+// side) and sums of 2^10 terms or more, or of 2^8 and more where the product has
+// 2^34 multiply-adds or more.  Workspaces above 24 GiB (12 bytes per operand
+// element) stay with the FP32 kernel, so that the largest steps (rank 32) still fit
+// beside their operands, and so do batches above 64.
 constexpr int kSplit32MinK = 10, kSplit32ShortK = 8, kSplit32ShortWork = 34;
 constexpr uint64_t kSplit32MaxBytes = uint64_t(24) << 30;
 struct Split32Shape {
   int m = -1, n = 0, k = 0, ksplit = 0;
+  int batch = 1, copies_a = 1, copies_b = 1;
   bool swap = false;               // B's free indices on the row side
   std::vector<int> Mf, Nf, K;      // row, column and summed labels
-  uint64_t hdr = 0, bytes_a = 0, bytes_b = 0, bytes_p = 0;
+  uint64_t hdr = 0, bytes_a = 0, bytes_b = 0, bytes_p = 0;  // A: the row operand
   uint64_t total() const { return hdr + bytes_a + bytes_b + bytes_p; }
+  // Whether it is faster than the FP32 kernel (plan: on operands that that one
+  // copies straight into LDS): times of both in us, fitted to measurements, with a
+  // margin of a tenth, and at most a quarter of the FP32 kernel's time for the
+  // packing, which an operand that is then flagged pays in vain.  This form / the FP32
+  // kernel on random / planner's layouts, (m, n, k) x batch: (8, 7, 10) 77 / 176 / 119,
+  // x 2 81 / 177 / 119, x 8 84 / 178 / 120, x 32 205 / 179 / 121 (estimated); (11, 10,
+  // 10) x 3 270 / 451 / 394; (8, 7, 13) x 32 915 / 1306 / 904; (13, 13, 8) 593 / 1136 /
+  // 813; (14, 13, 9) 1500 / 3970 / 3100; (12, 12, 12) 1340 / 3450 / 3070; below the line
+  // (14, 7, 10) 207 / 159 / 123, (15, 8, 10) 452 / 461 / 395.  Flagged: (8, 7, 10) 192,
+  // (11, 10, 10) x 3 508, (12, 12, 12) 3616.
+  bool pays(bool plan) const {
+    const double elems = std::ldexp(1.0, m + k) * copies_a + std::ldexp(1.0, n + k) * copies_b;
+    const double outs = std::ldexp((double)batch, m + n);
+    const double split = 60 + 6.5e-6 * elems + 16.4e-9 * std::ldexp(outs, k) +
+                         1.9e-6 * outs * (ksplit ? 1 + (2 << ksplit) : 1);
+    const double items = std::ldexp((double)batch, m + n - 13);  // 128 x 64 tiles
+    const double round = items <= 256 ? (plan ? 0.116 : 0.16)
+                                      : (plan ? 0.19 : 0.215) * std::ceil(items / 512);
+    const double fp32 = std::ldexp(round, k);
+    return split <= 0.9 * fp32 && 14 + 6e-6 * elems <= 0.25 * fp32;
+  }
 };
 
 Split32Shape split32_shape(const std::vector<int>& la, const std::vector<int>& lb,
-                           const std::vector<int>& lc, int32_t batch, int32_t kernel, int32_t prec) {
+                           const std::vector<int>& lc, int32_t batch, int64_t stride_a,
+                           int64_t stride_b, int32_t kernel, int32_t prec) {
   Split32Shape g;
-  if (prec != RQC_F32 || kernel != -1 || batch > 64) return g;
+  if (prec != RQC_F32 || kernel != -1 || batch > rqc::kSplitCopies) return g;
   int shared = 0;  // most calls end here
   for (int x : la) shared += std::find(lb.begin(), lb.end(), x) != lb.end();
   if (shared < kSplit32ShortK) return g;
@@ -505,18 +540,25 @@ Split32Shape split32_shape(const std::vector<int>& la, const std::vector<int>& l
   };
   c_order(g.Mf);
   c_order(g.Nf);
-  g.hdr = 256 + 8 * rqc::kSplitParts;  // header, then the partial maxima of A and of B
-  g.bytes_a = uint64_t(12) << (m + k);
-  g.bytes_b = uint64_t(12) << (n + k);
+  g.batch = batch;
+  g.copies_a = (g.swap ? stride_b : stride_a) && batch > 1 ? batch : 1;
+  g.copies_b = (g.swap ? stride_a : stride_b) && batch > 1 ? batch : 1;
+  // Header, partial maxima, packed operands, partial outputs.
+  g.hdr = sizeof(rqc::SplitHdr) + 2 * rqc::kSplitPartBytes;
+  g.bytes_a = ((uint64_t)g.copies_a << (m + k)) * 12;
+  g.bytes_b = ((uint64_t)g.copies_b << (n + k)) * 12;
   // Split the sum while the tiles cannot fill the GPU (one workgroup per CU),
   // keeping at least 16 chunks of 32 terms per split.
-  const uint64_t tiles = uint64_t(1) << (m - 8 + n - 7);
+  const uint64_t tiles = (uint64_t)batch << (m - 8 + n - 7);
   while ((tiles << g.ksplit) < 512 && k - 5 - g.ksplit > 4) ++g.ksplit;
-  if (g.ksplit) g.bytes_p = uint64_t(8) << (m + n + g.ksplit);
+  if (g.ksplit) g.bytes_p = ((uint64_t)batch << (m + n + g.ksplit)) * 8;
   if (g.total() > kSplit32MaxBytes) return g;
   g.m = m;
   g.n = n;
   g.k = k;
+  // A single product may bring operands of either layout; a batch that does not
+  // pay on any asks for no workspace.
+  if (batch > 1 && !g.pays(false)) g.m = -1;
   return g;
 }
 
@@ -573,61 +615,59 @@ std::vector<int8_t> frag_sources(const std::vector<int>& in, const std::vector<i
   return perm_sources(in, out);
 }
 
-// An FP32 call with a long sum (shape g): per copy the operands' maxima and
-// packing (a shared operand once), the GEMM, and the FP32 kernel, which runs
-// only if an operand was flagged.
+// An FP32 call with a long sum (shape g): the operands' maxima, packing and the look
+// at them, the GEMM, and the FP32 kernel (step f), which runs only if an operand
+// was flagged.
 void pair_split32(const Split32Shape& g, const std::vector<int>& la, const std::vector<int>& lb,
-                  const std::vector<int>& lc, const void* A, const void* B, void* C, int32_t batch,
-                  int64_t stride_a, int64_t stride_b, int64_t stride_c, char* ws, hipStream_t s) {
+                  const std::vector<int>& lc, rqc::StepDesc f, int kern, char* ws, hipStream_t s) {
   const std::vector<int>&lr = g.swap ? lb : la, &lcl = g.swap ? la : lb;  // row and column operand
   const std::vector<int8_t> src_r = frag_sources(lr, g.Mf, g.K),
                             src_c = frag_sources(lcl, g.Nf, g.K);
   rqc::SplitHdr* hdr = reinterpret_cast<rqc::SplitHdr*>(ws);
-  uint32_t* part_r = reinterpret_cast<uint32_t*>(ws + 256);
-  uint32_t* part_c = part_r + rqc::kSplitParts;
+  rqc::SplitOperand r{}, c{};
+  r.in = g.swap ? f.B : f.A;
+  r.out = ws + g.hdr;
+  r.stride_in = g.swap ? f.sB_s : f.sA_s;
+  r.copies = g.copies_a;
+  r.rank = g.m + g.k;
+  r.part = ws + sizeof(rqc::SplitHdr);
+  r.src_of_out = src_r.data();
+  c.in = g.swap ? f.A : f.B;
+  c.out = r.out + g.bytes_a;
+  c.stride_in = g.swap ? f.sA_s : f.sB_s;
+  c.copies = g.copies_b;
+  c.rank = g.n + g.k;
+  c.part = ws + sizeof(rqc::SplitHdr) + rqc::kSplitPartBytes;
+  c.src_of_out = src_c.data();
+  for (rqc::SplitOperand* o : {&r, &c}) {
+    o->stride_out = int64_t(4) << o->rank;
+    o->plane = o->stride_out * o->copies;
+  }
+  rqc::hip_check(rqc::launch_split_pack(r, c, g.k, hdr, s), "pack FP32 halves");
   rqc::FragDesc d{};
-  d.copies = 1;
-  d.A = ws + g.hdr;
-  d.B = d.A + g.bytes_a;
+  d.copies = g.batch;
+  d.A = r.out;
+  d.B = c.out;
+  d.C = f.C;
   d.hdr = hdr;
-  d.plane_a = (int64_t)(g.bytes_a / 3);
-  d.plane_b = (int64_t)(g.bytes_b / 3);
+  d.sA = g.copies_a > 1 ? r.stride_out : 0;
+  d.sB = g.copies_b > 1 ? c.stride_out : 0;
+  d.sC = f.sC_s;
+  d.plane_a = r.plane;
+  d.plane_b = c.plane;
   d.m = g.m, d.n = g.n, d.k = g.k;
   d.ksplit = g.ksplit;
-  d.P = g.ksplit ? reinterpret_cast<float2*>(ws + g.hdr + g.bytes_a + g.bytes_b) : nullptr;
+  d.P = g.ksplit ? reinterpret_cast<float2*>(c.out + g.bytes_b) : nullptr;
   const int rank_c = (int)lc.size();
   auto c_bit = [&](int label) {
     return (int8_t)(rank_c - 1 - (std::find(lc.begin(), lc.end(), label) - lc.begin()));
   };
   for (int b = 0; b < g.m; ++b) d.crow[b] = c_bit(g.Mf[g.m - 1 - b]);
   for (int b = 0; b < g.n; ++b) d.ccol[b] = c_bit(g.Nf[g.n - 1 - b]);
-  int kern = rqc::KERN_MFMA;
-  rqc::StepDesc f = rqc::make_pair_desc(la, lb, lc, kern);
-  f.variant = rqc::kVarPersistent;
+  rqc::hip_check(rqc::launch_split_gemm(d, s), "split FP32 GEMM");
   f.run_if = hdr;
-  for (int32_t j = 0; j < batch; ++j) {
-    const float2* a = static_cast<const float2*>(A) + j * stride_a;
-    const float2* b = static_cast<const float2*>(B) + j * stride_b;
-    float2* c = static_cast<float2*>(C) + j * stride_c;
-    const int64_t stride_r = g.swap ? stride_b : stride_a, stride_l = g.swap ? stride_a : stride_b;
-    if (j == 0 || stride_r)
-      rqc::hip_check(rqc::launch_split_pack(g.swap ? b : a, const_cast<char*>(d.A), (int)lr.size(),
-                                            src_r.data(), d.plane_a, false, part_r, &hdr->flag_a,
-                                            &hdr->exp_a, s),
-                     "pack rows");
-    if (j == 0 || stride_l)
-      rqc::hip_check(rqc::launch_split_pack(g.swap ? a : b, const_cast<char*>(d.B), (int)lcl.size(),
-                                            src_c.data(), d.plane_b, true, part_c, &hdr->flag_b,
-                                            &hdr->exp_b, s),
-                     "pack columns");
-    d.C = c;
-    rqc::hip_check(rqc::launch_split_gemm(d, s), "split FP32 GEMM");
-    f.A = a;
-    f.B = b;
-    f.C = c;
-    rqc::hip_check(rqc::launch_step(f, kern, rqc::ST_C64, rqc::ST_C64, rqc::ST_C64, 0, s),
-                   "FP32 kernel for wide ranges");
-  }
+  rqc::hip_check(rqc::launch_step(f, kern, rqc::ST_C64, rqc::ST_C64, rqc::ST_C64, 0, s),
+                 "FP32 kernel for uneven operands");
 }
 
 // Labels of a pairwise call, validated (ranks, NULLs, repeats, batch).
@@ -663,7 +703,7 @@ rqc_status rqc_pair_workspace_bytes(const int32_t* labels_a, int32_t rank_a,
   std::vector<int> la, lb, lc;
   pair_labels(labels_a, rank_a, labels_b, rank_b, labels_c, rank_c, batch_count, la, lb, lc);
   const Gemm16Shape g = gemm16_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
-  const Split32Shape h = split32_shape(la, lb, lc, batch_count, kernel, prec);
+  const Split32Shape h = split32_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
   *bytes = g.m >= 0   ? g.total()
            : h.m >= 0 ? h.total()
                       : simt_split(la, lb, lc, batch_count, kernel, prec).bytes;
@@ -681,15 +721,19 @@ rqc_status rqc_pair_contract_ws(const int32_t* labels_a, int32_t rank_a, const i
   std::vector<int> la, lb, lc;
   pair_labels(labels_a, rank_a, labels_b, rank_b, labels_c, rank_c, batch_count, la, lb, lc);
   const Gemm16Shape g = gemm16_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
-  const Split32Shape h = split32_shape(la, lb, lc, batch_count, kernel, prec);
+  const Split32Shape h = split32_shape(la, lb, lc, batch_count, stride_a, stride_b, kernel, prec);
   // Operands and workspace as the packing needs them; the FP32 kernel runs
   // without a workspace, so a call that brings none (or less) still runs.
   if (h.m >= 0 && A && B && C && workspace && ws_bytes >= h.total() && (uintptr_t)workspace % 256 == 0 &&
       ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && stride_a % 2 == 0 && stride_b % 2 == 0 &&
       (batch_count == 1 || stride_c >= ((int64_t)1 << rank_c))) {
-    pair_split32(h, la, lb, lc, A, B, C, batch_count, stride_a, stride_b, stride_c,
-                 static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
-    return RQC_OK;
+    int kern = rqc::KERN_MFMA;
+    const rqc::StepDesc f =
+        pair_desc(la, lb, lc, kern, A, B, C, batch_count, stride_a, stride_b, stride_c);
+    if (h.pays(rqc::mfma32_copies(f))) {
+      pair_split32(h, la, lb, lc, f, kern, static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
+      return RQC_OK;
+    }
   }
   if (g.m < 0) {
     const SimtSplit sp = simt_split(la, lb, lc, batch_count, kernel, prec);
@@ -701,15 +745,7 @@ rqc_status rqc_pair_contract_ws(const int32_t* labels_a, int32_t rank_a, const i
       throw rqc::Error{RQC_EINVAL, "workspace smaller than rqc_pair_workspace_bytes"};
     if ((uintptr_t)workspace % 256) throw rqc::Error{RQC_EINVAL, "workspace not 256-byte aligned"};
     int kern = kernel;
-    rqc::StepDesc d = rqc::make_pair_desc(la, lb, lc, kern);
-    d.A = A;
-    d.B = B;
-    d.C = C;
-    d.sA_s = stride_a;
-    d.sB_s = stride_b;
-    d.sC_s = stride_c;
-    d.gs_c = batch_count;
-    d.copies = batch_count;
+    rqc::StepDesc d = pair_desc(la, lb, lc, kern, A, B, C, batch_count, stride_a, stride_b, stride_c);
     d.ksplit = sp.ks;
     d.P = static_cast<float2*>(workspace);
     d.p_stride = (int64_t)batch_count << rank_c;

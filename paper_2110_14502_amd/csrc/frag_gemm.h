@@ -68,7 +68,7 @@ __global__ __launch_bounds__(512, 1) void k_frag_gemm(FragDesc d) {
   __shared__ __attribute__((aligned(16))) char lds[3 * kFragBuf];
   __shared__ int64_t roff[kGemm16M];
   __shared__ int64_t coff[kGemm16N];
-  if (MODE == 0 && (d.hdr->flag_a | d.hdr->flag_b)) return;  // the FP32 kernel takes the product
+  if (MODE == 0 && d.hdr->flag) return;  // the FP32 kernel takes the product
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
   const uint64_t T = gridDim.x;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(512, 1) void k_frag_gemm(FragDesc d) {
   }
 
   typedef float f2v __attribute__((ext_vector_type(2)));
-  const int sh = MODE == 0 ? -(d.hdr->exp_a + d.hdr->exp_b) : 0;
+  const int sh = MODE == 0 ? -(d.hdr->exp_a[d.sA ? copy : 0] + d.hdr->exp_b[d.sB ? copy : 0]) : 0;
   f2v* Cf = d.ksplit ? reinterpret_cast<f2v*>(d.P) + ((copy << d.ksplit | (int64_t)ks) << (d.m + d.n))
                      : reinterpret_cast<f2v*>(d.C) + copy * d.sC;
 #pragma unroll

@@ -36,7 +36,7 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 template <int LP>
 __global__ __launch_bounds__(256) void k_pack16(const float2* in, char* out, PermTiles p,
                                                 uint32_t n_iter) {
-  permute_tiles(in, p, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
+  permute_tiles(in, p, blockIdx.x, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
     char* dst = out + frag_at(o);
     *reinterpret_cast<uint2*>(dst) = make_uint2(pack2<LP>(a.x, b.x), pack2<LP>(c.x, e.x));
     *reinterpret_cast<uint2*>(dst + kFragBytes) = make_uint2(pack2<LP>(a.y, b.y), pack2<LP>(c.y, e.y));
@@ -62,6 +62,7 @@ hipError_t launch_pack16(const void* in, char* out, int rank, const int8_t* src_
 // Split-K partials summed in split order (the result does not depend on
 // timing) and written to C in its layout: one thread per output element.
 __global__ __launch_bounds__(256) void k_gemm16_reduce(FragDesc d) {
+  if (d.hdr && d.hdr->flag) return;  // the FP32 kernel takes the product
   const uint64_t per = uint64_t(1) << (d.m + d.n);
   const uint64_t total = per * (uint64_t)d.copies;
   const int S = 1 << d.ksplit;

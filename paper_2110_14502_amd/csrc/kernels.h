@@ -24,10 +24,12 @@ struct TileMap {
 };
 
 // FP32 long sums on the FP16 matrix cores (k_split32.hip): start of the
-// workspace.  flag_*: the operand needs the FP32 kernel; exp_*: power-of-two
-// scales of the packed operands.
+// workspace.  flag: an operand needs the FP32 kernel; exp_*: power-of-two scales
+// of the packed copies of each operand.
+constexpr int kSplitCopies = 64;
 struct SplitHdr {
-  int32_t flag_a, flag_b, exp_a, exp_b;
+  int32_t flag, pad[63];
+  int32_t exp_a[kSplitCopies], exp_b[kSplitCopies];
 };
 
 // One pairwise contraction C[m,n] = sum_k A[m,k] B[k,n] with every index of
@@ -47,7 +49,7 @@ struct StepDesc {
   const float* maxB;
   float* maxC;
   int32_t* flag;  // per slice (js) non-finite flag, may be null
-  const SplitHdr* run_if;  // FP32 matrix-core kernel: return unless an operand is flagged; may be null
+  const SplitHdr* run_if;  // FP32 matrix-core kernels: return unless an operand is flagged; may be null
   float maxA_const, maxB_const;
   int64_t sA_s, sA_b, sB_s, sB_b, sC_s, sC_b;  // copy strides, elements
   int32_t eA_s, eA_b, eB_s, eB_b, eC_s, eC_b;  // copy strides, scale arrays
@@ -231,7 +233,7 @@ struct FragDesc {
   const SplitHdr* hdr;     // split halves only
   int64_t sA, sB, sC;      // copy strides: bytes of A and B (0 = shared), complex elements of C
   int64_t plane_a, plane_b;
-  int32_t m, n, k;         // bits: rows (>= 8), columns (>= 7), summed (>= 7)
+  int32_t m, n, k;         // bits: rows (>= 8), columns (>= 7), summed (>= 7; split halves: >= 5)
   int32_t copies;
   int32_t ksplit;          // the sum split 2^ksplit ways (partials in P, then reduced)
   float2* P;               // partials [copy][split][row][column], when ksplit > 0
@@ -246,13 +248,26 @@ hipError_t launch_gemm16(const FragDesc& d, int lp_kind, hipStream_t s);
 // C = the partials of a split sum added in split order.
 hipError_t launch_gemm16_reduce(const FragDesc& d, hipStream_t s);
 
-// FP32 long sums on the FP16 matrix cores: largest components, then packing, of
-// one operand (`right` for B), 12 bytes per element in all.
-constexpr int kSplitParts = 1024;  // partial maxima per operand
-hipError_t launch_split_pack(const void* in, char* out, int rank, const int8_t* src_of_out,
-                             int64_t plane, bool right, uint32_t* part, int32_t* flag,
-                             int32_t* scale_exp, hipStream_t s);
+// FP32 long sums on the FP16 matrix cores: one operand of the product, `copies`
+// (at most kSplitCopies) tensors of 2^rank values stride_in elements apart, and its
+// packed form (three planes of 4 bytes per element, stride_out bytes from copy to
+// copy); part: kSplitPartBytes of partial results; src_of_out as for launch_pack16.
+constexpr int kSplitParts = 1024, kSplitPartBytes = 16 * kSplitParts;
+struct SplitOperand {
+  const void* in;
+  char* out;
+  int64_t stride_in, stride_out, plane;
+  void* part;
+  int32_t rank, copies;
+  const int8_t* src_of_out;
+};
+// Packs A (rows) and B (columns), sums over 2^k terms, and sets the header.
+hipError_t launch_split_pack(const SplitOperand& a, const SplitOperand& b, int k, SplitHdr* hdr,
+                             hipStream_t s);
 hipError_t launch_split_gemm(const FragDesc& d, hipStream_t s);
+// Whether the FP32 matrix-core step d (complex64 operands) is copied straight into
+// LDS (k_mfma32_copy).
+bool mfma32_copies(const StepDesc& d);
 hipError_t launch_cgemm(int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
                         hipStream_t s);
 

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) void k_permute(const float2* in, float2* out, 
 
 __global__ __launch_bounds__(256) void k_permute_tiles(const float2* in, float2* out, PermTiles p,
                                                        uint32_t n_iter) {
-  permute_tiles(in, p, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
+  permute_tiles(in, p, blockIdx.x, n_iter, [&](int64_t o, float2 a, float2 b, float2 c, float2 e) {
     float4* q = reinterpret_cast<float4*>(out + o);
     q[0] = make_float4(a.x, a.y, b.x, b.y);
     q[1] = make_float4(c.x, c.y, e.x, e.y);

@@ -11,6 +11,7 @@ constexpr int kPermBits = 12;                              // tile bits
 constexpr int kPermGroups = (1 << kPermBits) / (4 * 256);  // groups of four elements per thread
 struct PermTiles {
   int32_t n_outer;
+  int32_t gbits;            // 2^gbits workgroups walk the tiles
   int32_t aligned;          // the input is 16-byte aligned
   int8_t tin[kPermBits];    // input address bit of read-order bit i (ascending)
   int8_t slot[kPermBits];   // output-order bit of read-order bit i
@@ -21,16 +22,17 @@ struct PermTiles {
 // LDS element of output-order index s: two elements of padding per 32.
 __device__ __forceinline__ int perm_pad(int s) { return s + 2 * (s >> 5); }
 
-// 256 threads; put(o, a, b, c, e) stores output elements o .. o + 3.
+// 256 threads, workgroup `block` of the 2^gbits; put(o, a, b, c, e) stores output
+// elements o .. o + 3.
 template <class Put>
-__device__ __forceinline__ void permute_tiles(const float2* in, const PermTiles& p, uint32_t n_iter,
-                                              Put put) {
+__device__ __forceinline__ void permute_tiles(const float2* in, const PermTiles& p, uint32_t block,
+                                              uint32_t n_iter, Put put) {
   __shared__ __attribute__((aligned(16))) float2 tile[(1 << kPermBits) + 2 * (1 << (kPermBits - 5))];
   __shared__ int64_t step_in[32], step_out[32];
   const int tid = threadIdx.x;
-  // Tile of iteration i: outer bits blockIdx.x + gridDim.x * i (the grid is a
-  // power of two); i -> i + 1 moves the bases by step[ctz(i + 1)].
-  const int gbits = 31 - __clz((int)gridDim.x);
+  // Tile of iteration i: outer bits block + 2^gbits i; i -> i + 1 moves the
+  // bases by step[ctz(i + 1)].
+  const int gbits = p.gbits;
   if (tid < p.n_outer - gbits) {
     int64_t si = int64_t(1) << p.oin[gbits + tid], so = int64_t(1) << p.oout[gbits + tid];
     for (int j = 0; j < tid; ++j) {
@@ -42,7 +44,7 @@ __device__ __forceinline__ void permute_tiles(const float2* in, const PermTiles&
   }
   int64_t base_in = 0, base_out = 0;
   for (int b = 0; b < gbits; ++b)
-    if ((blockIdx.x >> b) & 1u) {
+    if ((block >> b) & 1u) {
       base_in += int64_t(1) << p.oin[b];
       base_out += int64_t(1) << p.oout[b];
     }
@@ -162,9 +164,9 @@ inline bool plan_permute_tiles(int rank, const int8_t* src_of_out, PermTiles& t,
     t.tin[at] = (int8_t)inb[i];
     t.slot[at] = (int8_t)i;
   }
-  const int gbits = no < 10 ? no : 10;
-  grid = 1u << gbits;
-  n_iter = 1u << (no - gbits);
+  t.gbits = no < 10 ? no : 10;
+  grid = 1u << t.gbits;
+  n_iter = 1u << (no - t.gbits);
   return true;
 }
 

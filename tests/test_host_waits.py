@@ -41,7 +41,7 @@ def _source(name):
 
 
 @pytest.mark.parametrize("source,kernel,n_kernels", [("k_gemm16.hip", "k_frag_gemm", 2), ("k_split32.hip", "k_frag_gemm", 1),
-                                                     ("k_mfma32.hip", "k_mfma32_copy", 3)])
+                                                     ("k_mfma32.hip", "k_mfma32_copy", 4)])
 def test_lds_reads_end_before_barriers(source, kernel, n_kernels, tmp_path):
     found = 0
     for name, lines in _assembly(_source(source), tmp_path).items():
