@@ -302,18 +302,21 @@ bool step_lp_store(const rqc_plan* p, int prec, size_t i) {
 
 // The form of the 16-bit matrix kernel for a step with a 16-bit stored A that
 // was not tuned (the sums are the same in all of them: the same bits).
-// Measured in FP16, us, 32 copies, two output orders each; (m, n, k): default /
-// streamed / exchanged:
-//   B complex64 (converted once per tile by the streamed form, per chunk by
-//   the others): (18, 6, 5) 1066 / 948; (16, 6, 6) 337 / 307; (14, 6, 6) 81 / 83;
-//   (15, 7, 5) 233 / 192 / 231; (14, 8, 6) 332 / 303 / 293; k = 7: (16, 7, 7)
-//   844 / 814 / 789 (as a step of a 6x6 call 807 / - / 853), (14, 8, 7) 384 /
-//   377 / 393, (13, 7, 7) 102 / 106 / 104.  So streamed up to k = 6; at k = 7 no
-//   form is better on all orders.
-//   B in 16 bits: (16, 7, 7) 797 / 820 / 689; (16, 7, 5) 528 / 475 / 409;
-//   (13, 7, 7) 93 / 104 / 93; (14, 8, 6) 265 / 260 / 260.  So exchanged where B
-//   fills a row tile; below, (18, 6, 5) 1020 / 948, (14, 6, 5) 64 / 62, (17, 6,
-//   6) 609 / 597, (14, 6, 6) 77 / 82: streamed at k = 5, at k = 6 from 2^16 rows.
+// Measured in FP16, us, two output orders each, (m, n, k) x copies:
+//   B complex64 (converted once per tile by the streamed form, per chunk by the
+//   default one), default / streamed: (18, 6, 5) x 32 960 / 841, (15, 7, 5) x 32 241 /
+//   202, x 4 40.8 / 38.7, x 1 20.6 / 21.2; (13, 6, 5) x 32 37.9 / 36.6, x 8 19.9 /
+//   20.6; (16, 6, 6) x 32 305 / 287, x 2 30.7 / 31.8; (14, 8, 6) x 32 283 / 260, x 1
+//   21.5 / 23.0.  So streamed up to k = 6, from 2^11 tiles of 128 x 64 on at k = 5 and
+//   2^12 at k = 6 (stream_pays; the fewer, the less of A there is to stream past a
+//   tile of B); at k = 7 no form is better on all orders (as a step of a 6x6 call
+//   (16, 7, 7) takes 807 by default and 853 exchanged).
+//   B in 16 bits, default / exchanged: (15, 7, 5) x 32 227 / 204, x 1 20.4 / 19.9; (15,
+//   7, 6) x 32 281 / 252, x 1 21.8 / 20.9; (16, 8, 6) x 32 989 / 981; (16, 7, 7) x 32 680 /
+//   674, x 1 32.4 / 32.2; (15, 7, 7) x 32 339 / 344, but (14, 7, 7) as a step of a 6x6
+//   call 37 less exchanged; (14, 8, 7) x 8 88 / 93.  So exchanged where B fills a row
+//   tile, at k = 7 exactly one.  Below: (18, 6, 5) x 32 905 / 840 streamed, (17, 6, 6)
+//   x 8 149 / 162: streamed at k = 5.
 static int32_t mfma16_variant(const rqc_plan* p, int prec, const Step& st) {
   auto lp = [&](int node) {
     const int i = p->pd.step_of_node[node];
@@ -321,8 +324,12 @@ static int32_t mfma16_variant(const rqc_plan* p, int prec, const Step& st) {
   };
   if (!lp(st.a) || st.k < 5 || st.m < 13) return 0;
   if (!lp(st.b)) return st.k <= 6 ? kVarStream : 0;
-  if (st.n >= 7) return st.m > st.n ? kVarSwap : 0;
-  return st.k == 5 || (st.k == 6 && st.m >= 16) ? kVarStream : 0;
+  if (st.n >= 7) return st.m > st.n && (st.k < 7 || st.n == 7) ? kVarSwap : 0;
+  return st.k == 5 ? kVarStream : 0;
+}
+
+static bool stream_pays(const Step& st, int copies) {
+  return (int64_t)copies << (st.m + st.n) >= int64_t(1) << (13 + (st.k == 5 ? 11 : 12));
 }
 
 void select_steps(rqc_plan* p) {
@@ -839,6 +846,9 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
           continue;
         }
         StepDesc d = bind_step(p, L, W, ws, i, gsc, gbc, gflags + g0, bias);
+        // (The tuner's choice stands: it was timed at its group's copies.)
+        if ((d.variant & kVarStream) && p->tuned_kern[L.prec][i] < 0 && !stream_pays(st, d.copies))
+          d.variant &= ~kVarStream;
         const Placement &A = L.place[st.a], &B = L.place[st.b], &C = L.place[st.node];
         const int kern = p->sel_kern[L.prec][i];
         const bool timed = p->timing_kernel == kTimeAll || kern == p->timing_kernel ||
