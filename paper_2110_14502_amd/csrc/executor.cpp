@@ -146,6 +146,14 @@ StepDesc make_pair_desc(const std::vector<int>& la, const std::vector<int>& lb,
   std::vector<int> Rt(Ms.begin(), Ms.begin() + rt), Ro(Ms.begin() + rt, Ms.end());
   std::vector<int> Nt(Ns.begin(), Ns.begin() + nt), No(Ns.begin() + nt, Ns.end());
   std::vector<int> Kt(Ks.begin(), Ks.begin() + kt), Ko(Ks.begin() + kt, Ks.end());
+  // Row kernel: a wave's 64 rows are the row bits lowest in C, so that its stores
+  // cover C's lowest address bits in any order of C; rows within 256 bytes of A stay
+  // together.  (17, 4, 4) x 32, C starting at row bits 0 and 1 / 6 and 7 / 0 and 6: 238 / 924
+  // / 435 us with the rows in A's order, 238 / 239 / 238 so; (16, 7, 4) x 8, C starting
+  // at row bits 4 to 7: 168.
+  if (kernel == KERN_ROWS && rt > 6)
+    std::stable_sort(Rt.begin() + std::max(0, 5 - k), Rt.end(), [&](int x, int y) { return pc(x) < pc(y); });
+  for (int i = 0; i < 8; ++i) d.rw_A[i] = (int8_t)(i < rt && kernel == KERN_ROWS ? pa(Rt[i]) - k : i);
   Ro = by(Ro, pc);
   No = by(No, pc);
   Ko = by(Ko, pa);

@@ -154,17 +154,18 @@ __device__ __forceinline__ void unpack_raw(const RawRow<S, K, NJ>& r, int g, flo
   }
 }
 
-// This lane's raw quarters of its four rows of a 256-row tile, K chunk kc.
-// Rows past the tile's R read row R-1 instead (their products are never
+// This lane's raw quarters of its four rows of a 256-row tile, K chunk kc: row
+// `first` (of this lane and wave) and the ones that x0 and x1 (block bits 0 and 1)
+// lead to.  Rows past the tile's R read row R-1 instead (their products are never
 // staged): with no load under a per-lane condition the prefetch's wait
 // counts stay exact, so multiplying a chunk does not wait for the next one.
 template <int SA, int K, int NJ>
 __device__ __forceinline__ void load_tile_rows(const StepDesc& d, int64_t oA, int KT, int kc,
-                                               int R, int wave, int lc, int g,
+                                               int R, int first, int x0, int x1, int g,
                                                RawRow<SA, K, NJ> (&dst)[4]) {
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb) {
-    const int r0 = wave * 64 + rb * 16 + lc;
+    const int r0 = first + (rb & 1 ? x0 : 0) + (rb & 2 ? x1 : 0);
     const int r = r0 < R ? r0 : R - 1;
     load_raw<SA, K, NJ>(d.A, oA + (int64_t)r * KT + kc * K, g, dst[rb]);
   }
@@ -229,6 +230,11 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
   const uint64_t n_tiles = n_rt * (uint64_t)d.copies;
   const int nC = (R < 64 ? R : 64) * NC;  // a wave's elements per chunk of columns
   const bool wrows = wave * 64 < R;       // whether this wave has rows
+  // A's rows of this lane (rw_A; one past the tile's last for rows it does not have).
+  const int x0 = 1 << d.rw_A[4], x1 = 1 << d.rw_A[5];
+  int first = ((wave & 1) << d.rw_A[6]) + ((wave >> 1) << d.rw_A[7]);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) first += ((lc >> b) & 1) << d.rw_A[b];
   int64_t gwave = 0;                      // C offset of its first row in the tile
   if (R > 64 && (wave & 1)) gwave += int64_t(1) << d.rw_C[0];
   if (R > 128 && (wave & 2)) gwave += int64_t(1) << d.rw_C[1];
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
     const int copy = (int)(t >> rsh);
     int64_t oA, oB, oC;
     outer_offsets(d, t & rmask, 0, copy % d.gs_c, copy / d.gs_c, oA, oB, oC);
-    load_tile_rows<SA, K, NJ>(d, oA, KT, 0, R, wave, lc, g, a);
+    load_tile_rows<SA, K, NJ>(d, oA, KT, 0, R, first, x0, x1, g, a);
   }
   // Wait for the first tile's rows here (s_waitcnt vmcnt(0)): entering the
   // tile loop with those loads pending, the compiler's wait counting merges
@@ -324,7 +330,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
         // registers are handed over only after this chunk (or, for the next
         // tile, at its end), so the loads stay in flight meanwhile.
         if (kc + 1 < nkc) {
-          load_tile_rows<SA, K, NJ>(d, oA, KT, kc + 1, R, wave, lc, g, an);
+          load_tile_rows<SA, K, NJ>(d, oA, KT, kc + 1, R, first, x0, x1, g, an);
         } else if (last_cg && t + 1 < t_end) {
           const uint64_t tn = t + 1;
           int64_t pA;
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(256) void k_rows(StepDesc d) {
             int64_t pB, pC;
             outer_offsets(d, 0, 0, cn % d.gs_c, cn / d.gs_c, pA, pB, pC);
           }
-          load_tile_rows<SA, K, NJ>(d, pA, KT, 0, R, wave, lc, g, an);
+          load_tile_rows<SA, K, NJ>(d, pA, KT, 0, R, first, x0, x1, g, an);
         }
         if constexpr (LPM) {
           // MFMA j takes real k g*NJ + 8j .. +7 of every lane quarter: the raw

@@ -76,7 +76,9 @@ struct StepDesc {
   int32_t vec_c;      // 1: tile bits 0 and 1 are C's address bits 0 and 1 (4-element stores)
   int32_t variant;    // kernel variant bits (kVar*), chosen per step by the tuner; 0 = default
   int8_t nh_C[16];
-  int8_t rw_C[2];     // row kernel: C's address bits of row bits 6 and 7 (which wave)
+  // Row kernel: A's row bits taken as row bits 0 to 7 of a tile, and C's address bits
+  // of the last two (which wave).
+  int8_t rw_A[8], rw_C[2];
   int8_t ro_A[kMaxOuter], ro_C[kMaxOuter];
   int8_t no_B[kMaxOuter], no_C[kMaxOuter];
   int8_t ko_A[kMaxOuter], ko_B[kMaxOuter];
