@@ -624,6 +624,17 @@ def pair_contract_stored(A, B, C_out, labels_a, labels_b, labels_c, store_a, sto
     return C_out
 
 
+def _xeb_workspace(n_amps, n_samples):
+    need = C.c_uint64()
+    _check(_lib.rqc_batch_xeb_workspace_bytes(int(n_amps), int(n_samples), C.byref(need)))
+    return need.value
+
+
+# The smallest batch that the library wants a workspace for (it asks for none
+# below, and asking it on each call costs 1 us of 25).
+_XEB_SPLIT = next(1 << b for b in range(64) if _xeb_workspace(1 << b, 0))
+
+
 def batch_xeb(amps, n_qubits, samples=None, stream=None):
     """FP64 statistics of an amplitude batch on the device (rqc_batch_xeb):
     amps is the float64 device tensor of (re, im) pairs that contract()
@@ -633,18 +644,17 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     ns = 0 if samples is None else samples.numel()
     sp = _ptr(samples) if samples is not None else None
     with _on_stream(stream, amps.device):
-        if n < 1 << 17 and ns < 1 << 17:  # no workspace (rqc.h); asking costs 1 us of 25
+        if n < _XEB_SPLIT and ns < _XEB_SPLIT:
             out = torch.empty(5, dtype=torch.float64, device=amps.device)
             _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
                                       _stream_handle(stream)))
             v = out.cpu().numpy()
         else:
-            need = C.c_uint64()
-            _check(_lib.rqc_batch_xeb_workspace_bytes(n, ns, C.byref(need)))
+            need = _xeb_workspace(n, ns)
             # The five results, then the workspace (one buffer, so one lifetime).
-            out = torch.empty(8 + need.value // 8, dtype=torch.float64, device=amps.device)
+            out = torch.empty(8 + need // 8, dtype=torch.float64, device=amps.device)
             _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                         C.c_void_p(out.data_ptr() + 64), need.value,
+                                         C.c_void_p(out.data_ptr() + 64), need,
                                          _stream_handle(stream)))
             v = out[:5].cpu().numpy()
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),

@@ -1,6 +1,9 @@
-"""Which single FP32 calls ask for the workspace of the form on the FP16 matrix
-cores (host only): long sums whose batch one launch of the FP32 kernel does in less
-time do not, and neither do short sums, small outputs and other kernels."""
+"""Which calls ask for a workspace (host only).
+
+Single FP32 calls, for the form on the FP16 matrix cores: long sums whose batch one
+launch of the FP32 kernel does in less time do not, and neither do short sums, small
+outputs and other kernels.  Batch statistics: from the size on that the binding has
+from the library itself."""
 import pytest
 
 import paper_2110_14502_amd as R
@@ -21,3 +24,8 @@ def test_batches_of_long_sums(m, n, k, batch, taken):
     assert (need >= 12 * batch * ((1 << (m + k)) + (1 << (n + k)))) == taken
     assert need == _need(n, m, k, batch)  # exchanged operands
     assert _need(m, n, k, batch, kernel=1) == 0
+
+
+def test_batch_statistics_threshold():
+    n = R._XEB_SPLIT
+    assert R._xeb_workspace(n, 0) and R._xeb_workspace(0, n) and not R._xeb_workspace(n - 1, n - 1)
