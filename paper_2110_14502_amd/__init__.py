@@ -6,7 +6,6 @@ module fails loudly when the native library has not been built.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes as C
 import json
 import os
@@ -228,14 +227,15 @@ def _stream_handle(stream=None):
     return C.c_void_p(int(torch.cuda.current_stream().cuda_stream))
 
 
-def _on_stream(stream, device):
-    """Context in which torch allocates for, and copies on, the stream that the
-    call's kernels run on: memory allocated and freed under another stream would
-    be handed out again while they still use it."""
-    import torch
+def _on_stream(stream, device, f):
+    """f() with torch allocating for, and copying on, the stream that the call's
+    kernels run on (None: the current one): memory allocated and freed under
+    another stream would be handed out again while they still use it."""
     if stream is None:
-        return contextlib.nullcontext()
-    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device=device))
+        return f()
+    import torch
+    with torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device=device)):
+        return f()
 
 
 def _ptr(t):
@@ -582,8 +582,8 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
     if need:
         if workspace is None:
             try:
-                with _on_stream(stream, A.device):
-                    workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
+                workspace = _on_stream(stream, A.device,
+                                       lambda: torch.empty(need, dtype=torch.uint8, device=A.device))
             except torch.OutOfMemoryError:
                 if prec != F32:
                     raise
@@ -643,20 +643,22 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     n = amps.numel() // 2
     ns = 0 if samples is None else samples.numel()
     sp = _ptr(samples) if samples is not None else None
-    with _on_stream(stream, amps.device):
+
+    def run():
         if n < _XEB_SPLIT and ns < _XEB_SPLIT:
             out = torch.empty(5, dtype=torch.float64, device=amps.device)
             _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
                                       _stream_handle(stream)))
-            v = out.cpu().numpy()
-        else:
-            need = _xeb_workspace(n, ns)
-            # The five results, then the workspace (one buffer, so one lifetime).
-            out = torch.empty(8 + need // 8, dtype=torch.float64, device=amps.device)
-            _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                         C.c_void_p(out.data_ptr() + 64), need,
-                                         _stream_handle(stream)))
-            v = out[:5].cpu().numpy()
+            return out.cpu().numpy()
+        need = _xeb_workspace(n, ns)
+        # The five results, then the workspace (one buffer, so one lifetime).
+        out = torch.empty(8 + need // 8, dtype=torch.float64, device=amps.device)
+        _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                     C.c_void_p(out.data_ptr() + 64), need,
+                                     _stream_handle(stream)))
+        return out[:5].cpu().numpy()
+
+    v = _on_stream(stream, amps.device, run)
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 

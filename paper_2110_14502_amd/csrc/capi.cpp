@@ -523,14 +523,15 @@ Split32Shape split32_shape(const std::vector<int>& la, const std::vector<int>& l
   if (prec != RQC_F32 || kernel != -1 || batch > rqc::kSplitCopies) return g;
   int shared = 0;  // most calls end here
   for (int x : la) shared += std::find(lb.begin(), lb.end(), x) != lb.end();
-  if (shared < kSplit32ShortK) return g;
+  const int fa = (int)la.size() - shared, fb = (int)lb.size() - shared;
+  if (shared < kSplit32ShortK || std::max(fa, fb) < 8 || std::min(fa, fb) < 7) return g;
   for (int x : la) (std::find(lb.begin(), lb.end(), x) != lb.end() ? g.K : g.Mf).push_back(x);
   for (int x : lb)
     if (std::find(la.begin(), la.end(), x) == la.end()) g.Nf.push_back(x);
   g.swap = g.Nf.size() > g.Mf.size();
   if (g.swap) std::swap(g.Mf, g.Nf);
   const int m = (int)g.Mf.size(), n = (int)g.Nf.size(), k = (int)g.K.size();
-  if (m < 8 || n < 7 || k > 24) return g;
+  if (k > 24) return g;
   if (k < kSplit32MinK && (k < kSplit32ShortK || m + n + k < kSplit32ShortWork)) return g;
   if (m + k > 36 || n + k > 36 || m + n > 36) return g;
   auto c_order = [&](std::vector<int>& v) {
