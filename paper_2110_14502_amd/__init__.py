@@ -635,30 +635,29 @@ def _xeb_workspace(n_amps, n_samples):
 _XEB_SPLIT = next(1 << b for b in range(64) if _xeb_workspace(1 << b, 0))
 
 
-def batch_xeb(amps, n_qubits, samples=None, stream=None):
-    """FP64 statistics of an amplitude batch on the device (rqc_batch_xeb):
-    amps is the float64 device tensor of (re, im) pairs that contract()
-    returns; samples an int64 device tensor of entry indices or None."""
+def _batch_xeb(amps, n_qubits, samples, stream):
     import torch
     n = amps.numel() // 2
     ns = 0 if samples is None else samples.numel()
     sp = _ptr(samples) if samples is not None else None
+    if n < _XEB_SPLIT and ns < _XEB_SPLIT:
+        out = torch.empty(5, dtype=torch.float64, device=amps.device)
+        _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                  _stream_handle(stream)))
+        return out.cpu().numpy()
+    need = _xeb_workspace(n, ns)
+    # The five results, then the workspace (one buffer, so one lifetime).
+    out = torch.empty(8 + need // 8, dtype=torch.float64, device=amps.device)
+    _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
+                                 C.c_void_p(out.data_ptr() + 64), need, _stream_handle(stream)))
+    return out[:5].cpu().numpy()
 
-    def run():
-        if n < _XEB_SPLIT and ns < _XEB_SPLIT:
-            out = torch.empty(5, dtype=torch.float64, device=amps.device)
-            _check(_lib.rqc_batch_xeb(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                      _stream_handle(stream)))
-            return out.cpu().numpy()
-        need = _xeb_workspace(n, ns)
-        # The five results, then the workspace (one buffer, so one lifetime).
-        out = torch.empty(8 + need // 8, dtype=torch.float64, device=amps.device)
-        _check(_lib.rqc_batch_xeb_ws(_ptr(amps), n, int(n_qubits), sp, ns, _ptr(out),
-                                     C.c_void_p(out.data_ptr() + 64), need,
-                                     _stream_handle(stream)))
-        return out[:5].cpu().numpy()
 
-    v = _on_stream(stream, amps.device, run)
+def batch_xeb(amps, n_qubits, samples=None, stream=None):
+    """FP64 statistics of an amplitude batch on the device (rqc_batch_xeb):
+    amps is the float64 device tensor of (re, im) pairs that contract()
+    returns; samples an int64 device tensor of entry indices or None."""
+    v = _on_stream(stream, amps.device, lambda: _batch_xeb(amps, n_qubits, samples, stream))
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kSimtBlock) void k_simt(StepDesc d) {
       const Scale sc = compute_scale(d, js, jb);
       float lmax = 0.f;
       int bad = 0;
-      if (q == 0 && lane < nC) store_out<SC>(d, oC + qg, acc[0], sc, lmax, bad);
+      if (q == 0 && lane < nC) store_out<SC, true>(d, oC + qg, acc[0], sc, lmax, bad);
       finish_scale<kSimtBlock>(d, js, jb, lmax, bad, red, ro == 0 && no == 0, sc);
       continue;
     }
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kSimtBlock) void k_simt(StepDesc d) {
     int bad = 0;
 #pragma unroll
     for (int i = 0; i < kSimtMaxC; ++i)
-      if (tid + i * kSimtBlock < nC) store_out<SC>(d, oC + cg[i], acc[i], sc, lmax, bad);
+      if (tid + i * kSimtBlock < nC) store_out<SC, true>(d, oC + cg[i], acc[i], sc, lmax, bad);
     finish_scale<kSimtBlock>(d, js, jb, lmax, bad, red, ro == 0 && no == 0, sc);
   }
 }
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(StepDesc d) {
             sy += v[i].y;
           }
       }
-      store_out<SC>(d, at, make_float2(sx, sy), sc, lmax, bad);
+      store_out<SC, true>(d, at, make_float2(sx, sy), sc, lmax, bad);
     }
     finish_scale<256>(d, js, jb, lmax, bad, red, ro == 0 && no == 0, sc);
   }
