@@ -338,16 +338,17 @@ hipError_t launch_permute(const void* in, void* out, int rank, const int8_t* src
 namespace rqc {
 
 // ---------------------------------------------------------------------------
-// Statistics of an amplitude batch in FP64 (fixed summation order, so the result does not depend on timing): sum |a|^2, sum |a|^4, and
-// the linear cross-entropy values derived from them; optionally the mean
-// |a|^2 over sampled entries of the batch (bounds-checked: an index outside
-// the batch makes that result NaN).
+// Statistics of an amplitude batch in FP64 (fixed summation order, so the result
+// does not depend on timing): sum |a|^2, sum |a|^4, and the linear cross-entropy
+// values derived from them; optionally the mean |a|^2 over sampled entries of the
+// batch (bounds-checked: an index outside the batch makes that result NaN).
 //
 // Batches of 2^17 amplitudes and more are read by many workgroups
 // (rqc_batch_xeb_ws): each writes four partial sums, and one workgroup adds
 // them in workgroup order; the split depends on the batch size alone.  One
-// workgroup reads 56 GB/s (601 us for 2^21 amplitudes, 33 MB; 32 us split), and up to 2^16 amplitudes stay in its reach: whole calls 30 us either way at
-// 2^16, 36 against 31 us at 2^17, 24 against 29 us at 2^10.
+// workgroup reads 56 GB/s (601 us for 2^21 amplitudes, 33 MB; 32 us split), and
+// up to 2^16 amplitudes stay in its reach: whole calls 30 us either way at 2^16, 36
+// against 31 us at 2^17, 24 against 29 us at 2^10.
 // ---------------------------------------------------------------------------
 constexpr int kStatThreads = 1024;
 
