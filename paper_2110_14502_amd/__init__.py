@@ -552,15 +552,24 @@ def to_complex(t):
 
 
 # ---------------------------------------------------------------- single steps
+def _labels(labels_a, labels_b, labels_c):
+    """The label arguments of a pairwise call."""
+    return (_i32(labels_a), len(labels_a), _i32(labels_b), len(labels_b), _i32(labels_c),
+            len(labels_c))
+
+
+def _pair_workspace(labels, kernel, batch, stride_a, stride_b, prec):
+    n = C.c_uint64()
+    _check(_lib.rqc_pair_workspace_bytes(*labels, int(batch), int(stride_a), int(stride_b),
+                                         int(kernel), int(prec), C.byref(n)))
+    return n.value
+
+
 def pair_workspace_bytes(labels_a, labels_b, labels_c, kernel=-1, batch=1, stride_a=0,
                          stride_b=0, prec=F32):
     """Device workspace (bytes) that a pair_contract call needs (0: none)."""
-    n = C.c_uint64()
-    _check(_lib.rqc_pair_workspace_bytes(_i32(labels_a), len(labels_a), _i32(labels_b),
-                                         len(labels_b), _i32(labels_c), len(labels_c), int(batch),
-                                         int(stride_a), int(stride_b), int(kernel), int(prec),
-                                         C.byref(n)))
-    return n.value
+    return _pair_workspace(_labels(labels_a, labels_b, labels_c), kernel, batch, stride_a,
+                           stride_b, prec)
 
 
 def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, batch=1,
@@ -577,8 +586,8 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
     if C_out is None:
         C_out = torch.empty(batch << len(labels_c), dtype=torch.complex64, device=A.device)
         stride_c = 1 << len(labels_c) if batch > 1 else stride_c
-    need = pair_workspace_bytes(labels_a, labels_b, labels_c, kernel, batch, stride_a, stride_b,
-                                prec)
+    labels = _labels(labels_a, labels_b, labels_c)
+    need = _pair_workspace(labels, kernel, batch, stride_a, stride_b, prec)
     if need:
         if workspace is None:
             try:
@@ -588,17 +597,14 @@ def pair_contract(A, B, labels_a, labels_b, labels_c, C_out=None, kernel=-1, bat
                 if prec != F32:
                     raise
     if need and workspace is not None:
-        _check(_lib.rqc_pair_contract_ws(_i32(labels_a), len(labels_a), _i32(labels_b),
-                                         len(labels_b), _i32(labels_c), len(labels_c), _ptr(A),
-                                         _ptr(B), _ptr(C_out), int(batch), int(stride_a),
-                                         int(stride_b), int(stride_c), int(kernel), int(prec),
-                                         _ptr(workspace), int(workspace.numel()),
+        _check(_lib.rqc_pair_contract_ws(*labels, _ptr(A), _ptr(B), _ptr(C_out), int(batch),
+                                         int(stride_a), int(stride_b), int(stride_c), int(kernel),
+                                         int(prec), _ptr(workspace), int(workspace.numel()),
                                          _stream_handle(stream)))
         return C_out
-    _check(_lib.rqc_pair_contract(_i32(labels_a), len(labels_a), _i32(labels_b), len(labels_b),
-                                  _i32(labels_c), len(labels_c), _ptr(A), _ptr(B), _ptr(C_out),
-                                  int(batch), int(stride_a), int(stride_b), int(stride_c),
-                                  int(kernel), int(prec), _stream_handle(stream)))
+    _check(_lib.rqc_pair_contract(*labels, _ptr(A), _ptr(B), _ptr(C_out), int(batch),
+                                  int(stride_a), int(stride_b), int(stride_c), int(kernel),
+                                  int(prec), _stream_handle(stream)))
     return C_out
 
 
@@ -657,7 +663,10 @@ def batch_xeb(amps, n_qubits, samples=None, stream=None):
     """FP64 statistics of an amplitude batch on the device (rqc_batch_xeb):
     amps is the float64 device tensor of (re, im) pairs that contract()
     returns; samples an int64 device tensor of entry indices or None."""
-    v = _on_stream(stream, amps.device, lambda: _batch_xeb(amps, n_qubits, samples, stream))
+    if stream is None:
+        v = _batch_xeb(amps, n_qubits, samples, None)
+    else:
+        v = _on_stream(stream, amps.device, lambda: _batch_xeb(amps, n_qubits, samples, stream))
     return {"sum_p": float(v[0]), "sum_p2": float(v[1]), "xeb_all": float(v[2]),
             "xeb_ideal_sampling": float(v[3]), "xeb_samples": float(v[4])}
 
