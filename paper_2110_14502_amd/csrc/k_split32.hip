@@ -38,8 +38,10 @@ namespace rqc {
 //   the modulus of the mean value squared at most 3/4 r0^2 (the rounding errors of
 //   nearly equal terms all add up: 0.1 to 1.5 times the FP32 kernel's);
 //   r0 at least 2^-14 of the operand's largest component.
-// It is raised also by an element that loses more than 2^-20 of itself, an infinity,
-// a NaN, or a largest component outside 2^+-100.  Rows and columns that are zero are
+// It is raised also by an element that loses more than 2^-18 of itself (one below
+// 2^-21 of the largest; what smaller losses add is 2^-25 of r0 and less, and a
+// tighter limit met a normal value in one product of 2^27 elements in a hundred), an
+// infinity, a NaN, or a largest component outside 2^+-100.  Rows and columns that are zero are
 // exact and pass.
 // Error against 64 bits of the rows and columns of C over the FP32 kernel's (median):
 // complex normal operands 0.80 at 2^8 terms, 0.77 at 2^10, 0.39 at 2^12 (with split
@@ -146,9 +148,9 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitArgs a) {
   m = stat_block(m);
   const uint32_t mx = max(m.re, m.im);
   const float big = __uint_as_float(mx);
-  // (A NaN fails both comparisons.)  With an eighth of the elements zero some row
-  // fails the look, and a real or imaginary operand fails it in every row: no
-  // need to pack those.
+  // (A NaN fails both comparisons.)  More than an eighth of the elements zero means
+  // rows with as many, and a real or imaginary operand fails the look in every row:
+  // those are not packed.
   if (mx != 0 && (!(big > 0x1p-100f && big < 0x1p100f) || m.re == 0 || m.im == 0 ||
                   m.zeros > 1u << (q.rank - 3))) {
     if (tid == 0) *a.flag = 1;
@@ -158,7 +160,7 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitArgs a) {
   const uint32_t block = at & ((1u << q.t.gbits) - 1);
   if (block == 0 && tid == 0) q.exps[copy] = sh;
   const float sc = ldexpf(1.f, sh);
-  int wide = 0;  // an element that two halves do not hold to 2^-20
+  int wide = 0;  // an element that two halves do not hold to 2^-18
   char* const out = q.out + copy * q.stride_out;
   const int64_t plane = q.plane;
   permute_tiles(reinterpret_cast<const float2*>(q.in + copy * q.stride_in), q.t, block, q.n_iter,
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(256) void k_split_pack(SplitArgs a) {
       im[i] = v[i].y * sc;
       const float rr = re[i] - (float)(_Float16)re[i], ri = im[i] - (float)(_Float16)im[i];
       const float er = fabsf(rr - (float)(_Float16)rr), ei = fabsf(ri - (float)(_Float16)ri);
-      if (fmaxf(er, ei) > 0x1p-20f * fmaxf(fabsf(re[i]), fabsf(im[i]))) wide = 1;
+      if (fmaxf(er, ei) > 0x1p-18f * fmaxf(fabsf(re[i]), fabsf(im[i]))) wide = 1;
     }
     char* dst = out + frag_at(o);
 #pragma unroll
