@@ -223,8 +223,9 @@ rqc_status rqc_plan_bind_memory(rqc_plan* p, void* dev_ptr, size_t bytes,
                                 rqc_stream stream);
 
 /* Workspace for a contraction of n_ids slices and n_batch bitstrings:
- * *min_bytes runs one slice and one bitstring at a time, *pref_bytes runs
- * everything in one group.  More workspace lets more slices run together. */
+ * *min_bytes runs one slice and one bitstring at a time (and small subtrees
+ * step by step where fusing them takes more), *pref_bytes runs everything in
+ * one group.  More workspace lets more slices run together. */
 rqc_status rqc_contract_workspace(const rqc_plan* p, uint64_t n_ids,
                                   uint64_t n_batch, int32_t prec,
                                   size_t* min_bytes, size_t* pref_bytes);

@@ -151,8 +151,7 @@ rqc_status rqc_plan_create(const rqc_network* n, const rqc_plan_opts* opts, rqc_
     rqc::make_plan(p->pd);
     const size_t res = rqc::resident_bytes(p);
     if (o.hbm_budget_bytes) {
-      const rqc::GroupLayout& L1 = rqc::group_layout(p, RQC_F32, 1, 1);
-      const size_t need = res + (size_t)rqc::ws_layout(p, L1, 1, 1).total;
+      const size_t need = res + (size_t)rqc::least_workspace(p, RQC_F32, 1, 1);
       if (need > o.hbm_budget_bytes)
         throw rqc::Error{RQC_EHBM, "plan needs " + std::to_string(need) +
                                        " device bytes for one slice, above the budget"};
@@ -252,11 +251,10 @@ rqc_status rqc_contract_workspace(const rqc_plan* pc, uint64_t n_ids, uint64_t n
   if (prec != RQC_F32 && prec != RQC_F16 && prec != RQC_BF16) throw rqc::Error{RQC_EINVAL, "bad precision"};
   if (n_ids == 0) n_ids = uint64_t(1) << p->pd.sliced.size();
   if (n_batch == 0) throw rqc::Error{RQC_EINVAL, "n_batch must be positive"};
-  const rqc::GroupLayout& L1 = rqc::group_layout(p, prec, 1, 1);
-  if (min_bytes) *min_bytes = (size_t)rqc::ws_layout(p, L1, n_ids, n_batch).total;
+  if (min_bytes) *min_bytes = (size_t)rqc::least_workspace(p, prec, n_ids, n_batch);
   if (pref_bytes) {
     const int gs = (int)std::min<uint64_t>(n_ids, 4096), gb = (int)std::min<uint64_t>(n_batch, 4096);
-    const rqc::GroupLayout& L = rqc::group_layout(p, prec, gs, gb);
+    const rqc::GroupLayout& L = rqc::group_layout(p, prec, {gs, gb, true});
     *pref_bytes = (size_t)rqc::ws_layout(p, L, n_ids, n_batch).total;
   }
   return RQC_OK;

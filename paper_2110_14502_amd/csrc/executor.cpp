@@ -380,6 +380,7 @@ void select_steps(rqc_plan* p) {
     }
     p->chain[m] = plan_chains(p, m);
   }
+  p->no_chain.tree_of_step.assign(pd.steps.size(), -1);
   p->layouts.clear();
   p->groups.clear();
   clear_graphs(p);
@@ -467,7 +468,12 @@ void clear_graphs(rqc_plan* p) {
 // ---------------------------------------------------------------------------
 // Group memory layout
 // ---------------------------------------------------------------------------
-static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
+static const ChainPlan& chain_plan(const rqc_plan* p, const GroupLayout& L) {
+  return L.fused ? p->chain[L.prec] : p->no_chain;
+}
+
+static GroupLayout compute_layout(rqc_plan* p, int prec, const Group& g) {
+  const int gs = g.gs, gb = g.gb;
   PlanData& pd = p->pd;
   const int nn = (int)pd.tree.left.size();
   const int nl = pd.tree.n_leaves;
@@ -475,6 +481,7 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
   L.prec = prec;
   L.gs = gs;
   L.gb = gb;
+  L.fused = g.fused;
   L.place.assign(nn, Placement());
   // Exponents and maxima are kept in every precision (complex64 outputs are
   // normalised too); 16-bit storage only in reduced precision.
@@ -482,7 +489,7 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
   const bool lp_mode = prec != RQC_F32;
   const int lp_store = prec == RQC_F16 ? ST_F16 : ST_BF16;
   std::vector<int64_t> bytes(nn, 0);
-  const ChainPlan& ch = p->chain[prec];
+  const ChainPlan& ch = chain_plan(p, L);
   // Tensors inside a fused subtree have no place in memory: its own steps
   // but the root, and the leaves that only such steps read.
   std::vector<char> inside(nn, 0);
@@ -691,12 +698,12 @@ static GroupLayout compute_layout(rqc_plan* p, int prec, int gs, int gb) {
   return L;
 }
 
-const GroupLayout& group_layout(rqc_plan* p, int prec, int gs, int gb) {
-  auto key = std::make_tuple(prec, gs, gb);
+const GroupLayout& group_layout(rqc_plan* p, int prec, const Group& g) {
+  auto key = std::make_tuple(prec, g.gs, g.gb, g.fused);
   auto it = p->layouts.find(key);
   if (it != p->layouts.end()) return it->second;
   if (p->layouts.size() > 64) p->layouts.clear();
-  return p->layouts.emplace(key, compute_layout(p, prec, gs, gb)).first->second;
+  return p->layouts.emplace(key, compute_layout(p, prec, g)).first->second;
 }
 
 WsLayout ws_layout(rqc_plan* p, const GroupLayout& L, uint64_t n_ids, uint64_t n_batch) {
@@ -801,7 +808,7 @@ void record_call(rqc_plan* p, const GroupLayout& L, const WsLayout& W, uint64_t 
     if (P.e_off < 0) return nullptr;
     return reinterpret_cast<int32_t*>(P.resident ? p->res + P.e_off : scale + P.e_off);
   };
-  const ChainPlan& ch = p->chain[L.prec];
+  const ChainPlan& ch = chain_plan(p, L);
   const char* blob = ws + W.jobs_off;
   ChainArgs ca{};
   ca.comps = reinterpret_cast<const ChainComp*>(blob + L.comps_off);
@@ -917,45 +924,61 @@ void upload_inputs(const GroupLayout& L, const WsLayout& W, char* ws, const uint
   hip_check(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, s), "call inputs");
 }
 
-bool fits(rqc_plan* p, int prec, int gs, int gb, uint64_t n_ids, uint64_t n_batch,
-          size_t ws_bytes) {
-  GroupLayout L = compute_layout(p, prec, gs, gb);
+static bool fits(rqc_plan* p, int prec, const Group& g, uint64_t n_ids, uint64_t n_batch,
+                 size_t ws_bytes) {
+  GroupLayout L = compute_layout(p, prec, g);
   return (size_t)ws_layout(p, L, n_ids, n_batch).total <= ws_bytes;
+}
+
+int64_t least_workspace(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch) {
+  const int64_t fused = ws_layout(p, group_layout(p, prec, {1, 1, true}), n_ids, n_batch).total;
+  const int64_t steps = ws_layout(p, group_layout(p, prec, {1, 1, false}), n_ids, n_batch).total;
+  return std::min(fused, steps);
+}
+
+// Bitstrings per group, one slice at a time: max_gb, halved until the call
+// fits.  Fused subtrees first; the roots of those that run in the first launch
+// are all held at once and their program is part of the workspace, which can
+// take more (52992 bytes on 271360 for a 5x5 circuit of depth 10) than the
+// leaves and small tensors they save.  A call that they alone would not let
+// into its workspace runs every step in a launch of its own.
+static bool bits_per_group(rqc_plan* p, int prec, int max_gb, uint64_t n_ids, uint64_t n_batch,
+                           size_t ws_bytes, Group& g) {
+  for (bool fused : {true, false}) {
+    g = {1, max_gb, fused};
+    while (g.gb > 1 && !fits(p, prec, g, n_ids, n_batch, ws_bytes)) g.gb = (g.gb + 1) / 2;
+    if (fits(p, prec, g, n_ids, n_batch, ws_bytes)) return true;
+  }
+  return false;
 }
 
 // Trying a group size lays the whole call out (50-150 us of host time each, a
 // dozen tries), so the sizes found are kept per call shape until the steps'
 // kernels or the group limits change.
-void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_t ws_bytes,
-                  int& gs, int& gb) {
+Group choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_t ws_bytes) {
   const auto key = std::make_tuple(prec, n_ids, n_batch, ws_bytes);
   const auto hit = p->groups.find(key);
-  if (hit != p->groups.end()) {
-    gs = hit->second.first;
-    gb = hit->second.second;
-    return;
-  }
+  if (hit != p->groups.end()) return hit->second;
   int max_gs = (int)std::min<uint64_t>(n_ids, 4096);
   int max_gb = (int)std::min<uint64_t>(n_batch, 4096);
   if (p->group_limit_s > 0) max_gs = std::min(max_gs, p->group_limit_s);
   if (p->group_limit_b > 0) max_gb = std::min(max_gb, p->group_limit_b);
   // Copies per launch are bounded by the grid's y dimension.
-  gb = max_gb;
-  while (gb > 1 && !fits(p, prec, 1, gb, n_ids, n_batch, ws_bytes)) gb = (gb + 1) / 2;
-  if (!fits(p, prec, 1, gb, n_ids, n_batch, ws_bytes)) {
-    GroupLayout L = compute_layout(p, prec, 1, 1);
+  Group g;
+  if (!bits_per_group(p, prec, max_gb, n_ids, n_batch, ws_bytes, g))
     throw Error{RQC_EHBM, "workspace too small: need at least " +
-                              std::to_string(ws_layout(p, L, n_ids, n_batch).total) + " bytes"};
-  }
+                              std::to_string(least_workspace(p, prec, n_ids, n_batch)) + " bytes"};
   int lo = 1, hi = max_gs;
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
-    if ((int64_t)mid * gb <= 65535 && fits(p, prec, mid, gb, n_ids, n_batch, ws_bytes)) lo = mid;
+    if ((int64_t)mid * g.gb <= 65535 &&
+        fits(p, prec, {mid, g.gb, g.fused}, n_ids, n_batch, ws_bytes)) lo = mid;
     else hi = mid - 1;
   }
-  gs = lo;
+  g.gs = lo;
   if (p->groups.size() >= 64) p->groups.clear();
-  p->groups[key] = {gs, gb};
+  p->groups[key] = g;
+  return g;
 }
 
 void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t* bits,
@@ -989,13 +1012,12 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
       b[i] = bits[i];
     }
   }
-  int gs, gb;
-  choose_group(p, prec, n_ids, n_batch, ws_bytes, gs, gb);
-  const GroupLayout& L = group_layout(p, prec, gs, gb);
+  const Group g = choose_group(p, prec, n_ids, n_batch, ws_bytes);
+  const GroupLayout& L = group_layout(p, prec, g);
   const WsLayout W = ws_layout(p, L, n_ids, n_batch);
   char* ws = static_cast<char*>(ws_v);
   upload_inputs(L, W, ws, ids.data(), n_ids, b, r.staging, s);
-  GraphKey key{prec, gs, gb, n_ids, n_batch, ws_v, out, per_slice};
+  GraphKey key{prec, g.gs, g.gb, g.fused, n_ids, n_batch, ws_v, out, per_slice};
   auto it = p->graphs.find(key);
   int reused = 0;
   if (p->timing_kernel >= 0 || direct) {
@@ -1058,8 +1080,8 @@ void contract(rqc_plan* p, const uint64_t* ids_in, uint64_t n_ids, const uint8_t
   r.flags_off = W.flags_off;
   r.out = out;
   r.per_slice = per_slice;
-  r.gs = gs;
-  r.gb = gb;
+  r.gs = g.gs;
+  r.gb = g.gb;
   r.graph_reused = reused;
   r.flops = (pd.flops_per_slice * (double)n_ids + pd.flops_per_bitstring) * (double)n_batch;
 }
@@ -1119,11 +1141,10 @@ void report(rqc_plan* p, PendingRun& r, hipStream_t s, rqc_run_report* rep, bool
   if (r.prec == RQC_F32) throw Error{RQC_ENUMERIC, "non-finite values in the FP32 contraction"};
   // Filter of Section 5.5, re-read: a slice whose reduced-precision result is
   // not finite is contracted again in FP32 instead of being discarded.
-  int gb = (int)std::min<uint64_t>(r.n_batch, 4096);
-  while (gb > 1 && !fits(p, RQC_F32, 1, gb, 1, r.n_batch, r.ws_bytes)) gb = (gb + 1) / 2;
-  if (!fits(p, RQC_F32, 1, gb, 1, r.n_batch, r.ws_bytes))
+  Group g32;
+  if (!bits_per_group(p, RQC_F32, (int)std::min<uint64_t>(r.n_batch, 4096), 1, r.n_batch, r.ws_bytes, g32))
     throw Error{RQC_EHBM, "workspace too small for the FP32 re-run"};
-  const GroupLayout& L = group_layout(p, RQC_F32, 1, gb);
+  const GroupLayout& L = group_layout(p, RQC_F32, g32);
   const WsLayout W = ws_layout(p, L, 1, r.n_batch);
   const int64_t ne2 = int64_t(2) << p->pd.net.open.size();  // doubles per bitstring
   const std::vector<LaunchRecord> keep_rec = p->trec;  // the probed call's records

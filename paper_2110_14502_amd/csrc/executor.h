@@ -44,6 +44,7 @@ struct ChainPlan {
 // Memory layout of one (precision, slices per group, bits per group).
 struct GroupLayout {
   int prec = RQC_F32, gs = 1, gb = 1;
+  bool fused = true;             // small subtrees in one launch each; else every step in its own
   std::vector<Placement> place;  // per tree node
   int64_t arena_bytes = 0;       // variable tensors
   int64_t scale_bytes = 0;       // exponent / max arrays
@@ -58,13 +59,14 @@ struct GroupLayout {
 
 struct GraphKey {
   int prec, gs, gb;
+  bool fused;
   uint64_t n_ids, n_batch;
   const void* ws;
   const void* out;
   const void* per_slice;
   bool operator<(const GraphKey& o) const {
-    return std::tie(prec, gs, gb, n_ids, n_batch, ws, out, per_slice) <
-           std::tie(o.prec, o.gs, o.gb, o.n_ids, o.n_batch, o.ws, o.out, o.per_slice);
+    return std::tie(prec, gs, gb, fused, n_ids, n_batch, ws, out, per_slice) <
+           std::tie(o.prec, o.gs, o.gb, o.fused, o.n_ids, o.n_batch, o.ws, o.out, o.per_slice);
   }
 };
 
@@ -106,6 +108,13 @@ struct GraphEntry {
   uint64_t last_use = 0;
 };
 
+// How a call is cut: slices and bitstrings per group, and whether its layout
+// fuses the small subtrees.
+struct Group {
+  int gs = 1, gb = 1;
+  bool fused = true;
+};
+
 // One probed launch of the timing hook.
 struct LaunchRecord {
   int step, kernel, m, n, k, copies, sa, sb, sc, variant;
@@ -141,6 +150,7 @@ struct rqc_plan {
   std::vector<rqc::StepDesc> sel_desc[3];
   std::vector<int> sel_kern[3];
   rqc::ChainPlan chain[3];              // fused small subtrees per precision mode
+  rqc::ChainPlan no_chain;              // of layouts that fuse nothing
   // Timing probe: events around launches of one kernel kind (or of all).
   int timing_kernel = -1;
   int group_limit_s = 0, group_limit_b = 0;  // 0: bounded by the workspace only
@@ -149,8 +159,8 @@ struct rqc_plan {
   std::vector<double> tms;              // per probed launch, after the report
   rqc_timing last_timing{};
   // Caches.
-  std::map<std::tuple<int, int, int>, rqc::GroupLayout> layouts;
-  std::map<std::tuple<int, uint64_t, uint64_t, size_t>, std::pair<int, int>> groups;
+  std::map<std::tuple<int, int, int, bool>, rqc::GroupLayout> layouts;
+  std::map<std::tuple<int, uint64_t, uint64_t, size_t>, rqc::Group> groups;
   std::map<rqc::GraphKey, rqc::GraphEntry> graphs;
   uint64_t graph_clock = 0;
   hipStream_t capture_stream = nullptr;
@@ -163,7 +173,7 @@ namespace rqc {
 
 size_t resident_bytes(rqc_plan* p);
 void bind_plan(rqc_plan* p, void* dev, size_t bytes, hipStream_t s);
-const GroupLayout& group_layout(rqc_plan* p, int prec, int gs, int gb);
+const GroupLayout& group_layout(rqc_plan* p, int prec, const Group& g);
 WsLayout ws_layout(rqc_plan* p, const GroupLayout& L, uint64_t n_ids, uint64_t n_batch);
 // Enqueue a contraction call on `s` (one graph launch); `run` keeps what the
 // report needs.
@@ -171,12 +181,11 @@ WsLayout ws_layout(rqc_plan* p, const GroupLayout& L, uint64_t n_ids, uint64_t n
 void contract(rqc_plan* p, const uint64_t* ids, uint64_t n_ids, const uint8_t* bits,
               uint64_t n_batch, int prec, void* ws, size_t ws_bytes, double* out,
               double* per_slice, hipStream_t s, PendingRun& run, bool direct = false);
-// Group sizes (slices, bitstrings) for a call within ws_bytes; EHBM if one
-// slice and one bitstring do not fit.
-void choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_t ws_bytes,
-                  int& gs, int& gb);
-bool fits(rqc_plan* p, int prec, int gs, int gb, uint64_t n_ids, uint64_t n_batch,
-          size_t ws_bytes);
+// The least workspace of a call: one slice and one bitstring at a time, with
+// or without fused subtrees.
+int64_t least_workspace(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch);
+// How to cut a call within ws_bytes; EHBM below the least workspace.
+Group choose_group(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, size_t ws_bytes);
 // Slice ids, closed bits and the device program to the call's workspace,
 // through `host` (kept by the caller while the copy may read it).
 void upload_inputs(const GroupLayout& L, const WsLayout& W, char* ws, const uint64_t* ids,

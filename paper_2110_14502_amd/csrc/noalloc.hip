@@ -48,8 +48,7 @@ rqc_status rqc_contract_noalloc(rqc_plan* p, const uint64_t* slice_ids, uint64_t
     if (n_batch == 0) throw rqc::Error{RQC_EINVAL, "n_batch must be positive"};
     // The smallest grouping (one slice and one bitstring at a time) must fit.
     const uint64_t ids = slice_ids ? n_ids : (uint64_t(1) << p->pd.sliced.size());
-    const rqc::GroupLayout& L1 = rqc::group_layout(p, prec, 1, 1);
-    const int64_t need = rqc::ws_layout(p, L1, ids, n_batch).total;
+    const int64_t need = rqc::least_workspace(p, prec, ids, n_batch);
     if (need > (int64_t)kScratchBytes)
       throw rqc::Error{RQC_EHBM, "call needs at least " + std::to_string(need) +
                                      " workspace bytes, above the 268435456-byte static scratch "

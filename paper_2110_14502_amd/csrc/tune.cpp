@@ -123,8 +123,8 @@ void autotune(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, void* ws_
   const uint64_t n_slices = uint64_t(1) << pd.sliced.size();
   if (n_ids == 0 || n_ids > n_slices) n_ids = n_slices;
   if (n_batch == 0) throw Error{RQC_EINVAL, "n_batch must be positive"};
-  int gs, gb;
-  choose_group(p, prec, n_ids, n_batch, ws_bytes, gs, gb);
+  const Group g = choose_group(p, prec, n_ids, n_batch, ws_bytes);
+  const int gs = g.gs, gb = g.gb;
   // Cached choices.
   std::map<std::string, std::pair<int, int>> cache;
   if (cache_path && *cache_path) {
@@ -138,7 +138,7 @@ void autotune(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, void* ws_
       if (is >> sig >> k >> v) cache[sig] = {k, v};
     }
   }
-  const GroupLayout L = group_layout(p, prec, gs, gb);  // copy: select_steps drops the cache
+  const GroupLayout L = group_layout(p, prec, g);  // copy: select_steps drops the cache
   const WsLayout W = ws_layout(p, L, (uint64_t)gs, (uint64_t)gb);
   char* ws = static_cast<char*>(ws_v);
   // One call on the first group fills the workspace with this plan's data
@@ -155,6 +155,7 @@ void autotune(rqc_plan* p, int prec, uint64_t n_ids, uint64_t n_batch, void* ws_
   Events ev;
   std::vector<std::pair<std::string, std::pair<int, int>>> learned;
   for (size_t i = 0; i < pd.steps.size(); ++i) {
+    // (A step that a larger workspace fuses stays as it is in this one too.)
     if (pd.steps[i].invariant || p->chain[prec].tree_of_step[i] >= 0) continue;
     const auto cand = candidates(p, prec, i);
     if (cand.empty()) continue;
